@@ -727,10 +727,29 @@ __global__ __launch_bounds__(256) void k_export_bc7(const float* __restrict__ ep
   }
 }
 
-// 8-bit planes: q = rint(fl32(255 v)) of values already projected to [0, 1].
-__global__ __launch_bounds__(256) void k_quant8(const float* __restrict__ src, uint8_t* __restrict__ dst, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    dst[i] = (uint8_t)min(max((int)rintf(__fmul_rn(255.0f, src[i])), 0), 255);
+// What an export writes beside the blocks, in one launch: 8-bit planes q = rint(fl32(255 v)) of
+// values already projected to [0, 1], and the decoder in mlp_dtype (NULL outputs are skipped).
+struct ExportTail {
+  const float *ut, *vt, *mlp;
+  uint8_t *fut, *fvt;
+  void* mlp_out;
+  int64_t nu, nv, nm;
+  int dt;
+};
+__global__ __launch_bounds__(256) void k_export_tail(ExportTail E) {
+  auto q8 = [](float v) { return (uint8_t)min(max((int)rintf(__fmul_rn(255.0f, v)), 0), 255); };
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < E.nu + E.nv + E.nm;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t v = i - E.nu, m = v - E.nv;
+    if (v < 0) {
+      if (E.fut) E.fut[i] = q8(E.ut[i]);
+    } else if (m < 0) {
+      if (E.fvt) E.fvt[v] = q8(E.vt[v]);
+    } else if (E.mlp_out) {
+      if (E.dt == NDGI_DTYPE_F16) ((_Float16*)E.mlp_out)[m] = (_Float16)E.mlp[m];
+      else ((float*)E.mlp_out)[m] = E.mlp[m];
+    }
+  }
 }
 
 // Import helpers: block endpoints (e1, e2) = (0, 1), so that the Eq. 7 lerp reads the weight
@@ -799,6 +818,14 @@ __global__ __launch_bounds__(256) void k_restore(const void* __restrict__ pred, 
 static int grid_of(int64_t n, int cap) {
   const int64_t w = (n + 255) / 256;
   return (int)(w < cap ? (w < 1 ? 1 : w) : cap);
+}
+
+static void launch_export_tail(const HybTrainDims& d, const float* P, const float* mlp, uint8_t* fut, uint8_t* fvt,
+                               void* mlp_out, int mlp_dtype, hipStream_t s) {
+  if (!fut && !fvt && !mlp_out) return;
+  const ExportTail E = {P + d.o_ut, P + d.o_vt, mlp, fut, fvt, mlp_out, (int64_t)d.Tt * d.U * 2, (int64_t)d.Tt * d.V * 2,
+                        d.n - d.o_mlp, mlp_dtype};
+  hipLaunchKernelGGL(k_export_tail, dim3(grid_of(E.nu + E.nv + E.nm, 1024)), dim3(256), 0, s, E);
 }
 
 static int check_htrain(const ndgi_hybrid_train_state* st, const char* who) {
@@ -974,12 +1001,9 @@ int ndgi_hybrid_export(ndgi_ctx* c, const ndgi_hybrid_train_state* st, int32_t m
     hipLaunchKernelGGL(k_export_bc4c, dim3(grid_of(nb_uvt, c->n_cu * 16)), dim3(256), 0, s, P + d.o_tep,
                        P + d.o_tw, d.Gu, d.Gv, 4, nb_uvt, fuvt_out);
   }
-  hipLaunchKernelGGL(k_quant8, dim3(grid_of((int64_t)d.Tt * d.U * 2, 1024)), dim3(256), 0, s, P + d.o_ut, fut_out,
-                     (int64_t)d.Tt * d.U * 2);
-  hipLaunchKernelGGL(k_quant8, dim3(grid_of((int64_t)d.Tt * d.V * 2, 1024)), dim3(256), 0, s, P + d.o_vt, fvt_out,
-                     (int64_t)d.Tt * d.V * 2);
+  launch_export_tail(d, P, mlp, fut_out, fvt_out, mlp_out, mlp_dtype, s);
   NDGI_HIP(hipGetLastError());
-  return launch_convert(c, mlp, mlp_out, mlp_dtype, d.n - d.o_mlp, s);
+  return NDGI_OK;
 }
 
 int ndgi_hybrid_encode(ndgi_ctx* c, const ndgi_hybrid_train_state* st, int32_t model, int32_t flags, int32_t codec,
@@ -1005,34 +1029,30 @@ int ndgi_hybrid_encode(ndgi_ctx* c, const ndgi_hybrid_train_state* st, int32_t m
   if (model < 0 || model >= d.M) return fail(NDGI_ERR_INVALID_ARG, "hybrid_encode: model %d of %d", model, d.M);
   const float* P = st->params + (int64_t)model * d.o_mlp;
   const float* mlp = st->params + (int64_t)d.M * d.o_mlp + (int64_t)model * (d.n - d.o_mlp);
-  TexSrc S = {};
-  S.codec = d.codec;
-  S.kind = direct ? kSrcDirect : (rounded ? kSrcRounded : kSrcLerp);
+  EncodeJob uv = {}, uvt = {};
+  uv.src.codec = uvt.src.codec = d.codec;
+  uv.src.kind = uvt.src.kind = direct ? kSrcDirect : (rounded ? kSrcRounded : kSrcLerp);
   const int per_fp = codec == NDGI_CODEC_BC7 ? 1 : 4;   // blocks per footprint
   if (fuv_out) {
-    S.ep = P;
-    S.w = P + d.o_uvw;
-    S.W = d.W;
-    S.H = d.H;
-    rc = launch_encode(S, codec, (int64_t)(d.H / 4) * (d.W / 4) * per_fp, fuv_out, c->n_cu, s);
-    if (rc) return rc;
+    uv.src.ep = P;
+    uv.src.w = P + d.o_uvw;
+    uv.src.W = d.W;
+    uv.src.H = d.H;
+    uv.n = (int64_t)(d.H / 4) * (d.W / 4) * per_fp;
+    uv.out = fuv_out;
   }
   if (fuvt_out) {
-    S.ep = P + d.o_tep;
-    S.w = P + d.o_tw;
-    S.W = d.Gu;
-    S.H = d.Gv;
-    rc = launch_encode(S, codec, (int64_t)d.S * (d.Gv / 4) * (d.Gu / 4) * per_fp, fuvt_out, c->n_cu, s);
-    if (rc) return rc;
+    uvt.src.ep = P + d.o_tep;
+    uvt.src.w = P + d.o_tw;
+    uvt.src.W = d.Gu;
+    uvt.src.H = d.Gv;
+    uvt.n = (int64_t)d.S * (d.Gv / 4) * (d.Gu / 4) * per_fp;
+    uvt.out = fuvt_out;
   }
-  if (fut_out)
-    hipLaunchKernelGGL(k_quant8, dim3(grid_of((int64_t)d.Tt * d.U * 2, 1024)), dim3(256), 0, s, P + d.o_ut, fut_out,
-                       (int64_t)d.Tt * d.U * 2);
-  if (fvt_out)
-    hipLaunchKernelGGL(k_quant8, dim3(grid_of((int64_t)d.Tt * d.V * 2, 1024)), dim3(256), 0, s, P + d.o_vt, fvt_out,
-                       (int64_t)d.Tt * d.V * 2);
+  rc = launch_encode(uv, uvt, codec, c->n_cu, s);
+  if (rc) return rc;
+  launch_export_tail(d, P, mlp, fut_out, fvt_out, mlp_out, mlp_dtype, s);
   NDGI_HIP(hipGetLastError());
-  if (mlp_out) return launch_convert(c, mlp, mlp_out, mlp_dtype, d.n - d.o_mlp, s);
   return NDGI_OK;
 }
 

@@ -68,7 +68,13 @@ struct TexSrc {
   int W, H, codec, kind;
 };
 // n blocks (BC7: footprints; BC4: footprint * 4 + channel for a map source) into out.
-int launch_encode(const TexSrc& S, int codec, int64_t n, uint8_t* out, int n_cu, hipStream_t s);
+struct EncodeJob {
+  TexSrc src;
+  int64_t n;
+  uint8_t* out;
+};
+// The blocks of both jobs (either may be empty).
+int launch_encode(const EncodeJob& ja, const EncodeJob& jb, int codec, int n_cu, hipStream_t s);
 int check_model(const ndgi_model* m, const char* who);
 int launch_decode(ndgi_ctx* ctx, const ndgi_model& m, const float* uvt, int64_t n, void* out, int prec,
                   hipStream_t s);
@@ -90,7 +96,6 @@ int check_hybrid(const ndgi_hybrid_model* m, const char* who);
 int launch_adam(ndgi_ctx* c, float* p, float* g, float* m, float* v, int64_t n, int64_t clamp_end, int64_t off_mlp,
                 float lr_feat, float lr_mlp, float beta1, float beta2, float eps, int64_t step, hipStream_t s);
 int launch_fill_zero(ndgi_ctx* c, float* p, int64_t n, hipStream_t s);
-int launch_convert(ndgi_ctx* c, const float* src, void* dst, int dt, int64_t n, hipStream_t s);
 int launch_hybrid_query(ndgi_ctx* ctx, const ndgi_hybrid_model& m, const float* uvt, int64_t n, void* out, int prec,
                         hipStream_t s);
 int launch_hybrid_pages(ndgi_ctx* ctx, const ndgi_hybrid_model* models, int32_t n_models, const ndgi_page_req* reqs,

@@ -746,12 +746,6 @@ int launch_fill_zero(ndgi_ctx* c, float* p, int64_t n, hipStream_t s) {
   NDGI_HIP(hipGetLastError());
   return NDGI_OK;
 }
-
-int launch_convert(ndgi_ctx* c, const float* src, void* dst, int dt, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_convert, dim3(grid_for(n, c->n_cu * 16)), dim3(256), 0, s, src, dst, dt, n);
-  NDGI_HIP(hipGetLastError());
-  return NDGI_OK;
-}
 }  // namespace ndgi
 
 extern "C" {

@@ -481,6 +481,26 @@ def test_bc7_encoder_matches_oracle_bit_for_bit(N, ctx):
                                   np.stack([O.bc7_decode_block(b) for b in got]))
 
 
+@pytest.mark.parametrize("n", [1, 3, 5, 24])
+def test_block_encoders_at_extremes_match_oracle(N, ctx, n):
+    """Blocks at the ends of the searches' ranges (values 0 and 255, one texel apart from the
+    rest, two values, steps of one), in counts around the four BC4 blocks of a workgroup: byte
+    for byte the oracle's."""
+    import torch
+    g = np.random.default_rng(147 + n)
+    one = np.full((n, 16, 4), 255)
+    one[np.arange(n), g.integers(0, 16, n)] = g.integers(0, 256, (n, 4))
+    kinds = [g.choice([0, 255], (n, 16, 4)), one, 255 - one,
+             np.where(g.random((n, 16, 1)) < 0.5, g.integers(0, 256, (n, 1, 4)), g.integers(0, 256, (n, 1, 4))),
+             np.clip(g.choice([0, 254], (n, 1, 1)) + g.integers(0, 2, (n, 16, 4)), 0, 255)]
+    tex = np.stack([kinds[i % len(kinds)][i] for i in range(n)]).astype(np.uint8)
+    got = N.bc7_encode_blocks(torch.from_numpy(tex).cuda()).cpu().numpy()
+    np.testing.assert_array_equal(got, O.encode_bc7(tex))
+    tex4 = np.ascontiguousarray(tex[..., 0])
+    got = N.bc4_encode_blocks(torch.from_numpy(tex4).cuda()).cpu().numpy()
+    np.testing.assert_array_equal(got, O.encode_bc4(tex4))
+
+
 def test_block_encoders_at_scale_match_oracle_on_a_sample(N, ctx):
     """65,536 blocks per encoder in one launch each (the grid-stride loops run many blocks
     per wave): a sample of them against the oracle, byte for byte, and every block decodes."""
