@@ -280,7 +280,7 @@ def run_c3(args, torch, N, I, ctx, frames=110, warm=10):
     mean_b = sum(fb) / len(fb)
     bound = "hbm" if sum(t_hbm) / len(t_hbm) >= t_mfma else "mfma"
     rl = dict(bound=bound, peak=HBM_PEAK_GBS if bound == "hbm" else MFMA_F16_PEAK_TFLOPS,
-              unit="GB/s" if bound == "hbm" else "TFLOP/s", traffic=None, kernel="k_decode_tiles (graph replay)",
+              unit="GB/s" if bound == "hbm" else "TFLOP/s", traffic=None, kernel="k_decode_pages<FP16> (graph replay)",
               bytes_per_launch=mean_b, flop_per_launch=texels * MLP_FLOP_PER_TEXEL)
     rl["achieved"] = (mean_b / (p50 * 1e-3) / 1e9 if bound == "hbm"
                       else texels * MLP_FLOP_PER_TEXEL / (p50 * 1e-3) / 1e12)
@@ -621,7 +621,7 @@ def main():
     frame_bytes = FRAME_BYTES_PER_TEXEL * W * H
     rl_frame = dict(bound="hbm", achieved=frame_bytes / (f16["frame_ms"] * 1e-3) / 1e9, peak=HBM_PEAK_GBS,
                     unit="GB/s", traffic=measured_traffic("frame_f16"),
-                    kernel="k_decode_tiles (+ k_decode_pages<FP16> for items off the tile path)",
+                    kernel="k_decode_pages<FP16>",
                     bytes_per_launch=frame_bytes)
     rl_frame["frac"] = rl_frame["achieved"] / HBM_PEAK_GBS
     rl_rand = dict(bound="hbm", achieved=RANDOM_COMPULSORY_BYTES / (f16["random_ms"] * 1e-3) / 1e9,

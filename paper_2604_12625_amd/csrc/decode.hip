@@ -1,4 +1,6 @@
 // Decode kernels: BC4 block decoder, random-access query decode, persistent page decode.
+#include <type_traits>
+
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -98,31 +100,32 @@ int launch_decode(ndgi_ctx* ctx, const ndgi_model& m, const float* uvt, int64_t 
 // -------------------------------------------------------------- persistent page decode
 // Work item = (request, sub-tile of 16*tw x 4*th texels).  Every wave of the persistent
 // grid takes items round-robin (items cost the same, so a static schedule balances
-// without a shared counter); a pass covers 16 columns x 4 rows: group q is row q.
-// ------------------------------------------------------------ texel-centre tile path
-// Used for FP16 decode of maps whose grid is a quarter of the texel resolution.  A pass
-// is 16 columns x 4 rows = exactly four 4x4 BC4 footprints.  The wave first decodes the
-// 4 footprints x 8 channels cooperatively (lane = footprint, channel, row pair) into LDS
-// and interpolates the grid window of the pass (6 x 3 nodes) in time into LDS; then each
-// group (one row) reads its lane share and runs the decoder.
+// without a shared counter).  A sub-tile is walked in slabs of 16 columns, top to bottom, in
+// passes of 4 rows: group q of a pass is its row q, lane (g, j) holds channels 2g, 2g+1 of
+// column j.
+//  * Blocks: two passes are eight BC4 footprints; lane (footprint, channel) decodes one whole
+//    block into wave-private LDS (the palette is built once for four rows), from which the
+//    groups read their bytes.
+//  * Grid: a lane needs, of each grid row, the two nodes around its column at both keys.  The
+//    four values are loaded into registers and folded by one set of weights (key x column)
+//    into a row sample, one row ahead of use; a texel row is then one lerp between the two
+//    row samples around it.  No grid value goes through LDS, and a row sample serves every
+//    texel row that it bounds.
+// The precision's decoder takes it from there.  Bound by VALU and matrix issue: about 224 VALU
+// and 32 MFMA a pass in FP16 (a kernel that staged each pass's time-blended grid window in LDS
+// took 250, and the maps off its quarter-resolution FP16 grid went to a second kernel, launched
+// after it in any case).  4096^2 FP16 frame 207 -> 191 us, 2000 pages of 32 maps 440 -> 397 us;
+// 1600 x 1152 in FP32 with a grid at an eighth of the texels 125 -> 73 us (there each texel
+// took its two texel_axis divisions, two integer block decodes and eight node loads alone).
+// Measured and not kept: the passes dealt out in equal contiguous runs, or in rounds of equal
+// parts of a run, instead of sub-tiles round-robin (197-209 us for the frame: more slab starts,
+// and neighbouring columns' lines written by different waves).
 
-struct TileLds {
-  uint32_t sp[8 * 20];   // decoded bytes [channel][row][16 columns]; channel stride 80 B
-                         // keeps the four lane groups of a read on distinct banks
-  float2 gt[18 * 4];     // [node row 0..2][node column 0..5][channel pair], time-blended
+struct PageLds {
+  uint32_t sp[2][8 * 20];   // decoded bytes of two passes: [channel][row][16 columns]; a channel
+                            // stride of 80 B keeps the four lane groups of a read on distinct banks
 };
 
-// Global loads of one pass: this lane's BC4 block (footprint db, channel dc) and its grid
-// window items (keys k0 and k1).  Issued one pass ahead of use.
-struct TileLoads {
-  uint2 blk;
-  uint32_t g0[2], g1[2];
-};
-
-// Addressing of a sub-tile's loads: the map's block and the two keys' grid planes as uniform
-// bases, and this lane's pass-invariant share (its block within a pass's four footprints and
-// its two grid window items).  Offsets are 32-bit: the model check bounds the map below 4 GiB
-// of blocks and the grid below 4 GiB.
 // The model's buffers are device memory: global address-space pointers let each load take a
 // uniform 64-bit base and a 32-bit lane offset (no 64-bit address arithmetic per lane).
 typedef const __attribute__((address_space(1))) uint8_t* gbyte_ptr;
@@ -130,151 +133,182 @@ template <typename T>
 __device__ __forceinline__ T gload(gbyte_ptr base, uint32_t byte_off) {
   return *(const __attribute__((address_space(1))) T*)(base + byte_off);
 }
-struct TileAddr {
-  gbyte_ptr bc4;        // the map's blocks
-  gbyte_ptr g0;         // grid of key k0: words of two FP16 channels
-  gbyte_ptr g1;         // key k1
-  int wb, gw, gw1, gh1;
-  uint32_t boff;        // byte offset of this lane's block in a pass: footprint db, channel dc
-  int nx[2], ny[2], pr[2];
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// A grid row as a lane needs it: channels 2g, 2g+1 of the nodes left and right of its column,
+// at the keys k0 and k1.
+template <int GDT> struct GridRaw;
+template <> struct GridRaw<NDGI_DTYPE_F16> { uint32_t v[4]; };
+template <> struct GridRaw<NDGI_DTYPE_F32> { float2 v[4]; };
+template <int GDT> struct GridCols {
+  static constexpr uint32_t kNode = GDT == NDGI_DTYPE_F16 ? 16u : 32u;   // bytes of a node
+  gbyte_ptr k0, k1;     // the keys' planes
+  uint32_t row;         // bytes of a grid row
+  uint32_t o0, o1;      // the lane's two nodes within a row
+  float w[4];           // (key, column) weights
 };
 
-__device__ __forceinline__ TileAddr tile_addr(const ndgi_model& m, const Keys& k, int lane, int db, int dc) {
-  TileAddr a;
-  const size_t plane_words = (size_t)m.Gh * m.Gw * 4;
-  a.bc4 = (gbyte_ptr)m.bc4;
-  a.g0 = (gbyte_ptr)m.grid + (size_t)k.k0 * plane_words * 4;
-  a.g1 = (gbyte_ptr)m.grid + (size_t)k.k1 * plane_words * 4;
-  a.wb = m.W >> 2;
-  a.gw = m.Gw;
-  a.gw1 = m.Gw - 1;
-  a.gh1 = m.Gh - 1;
-  a.boff = (uint32_t)(db * 64 + 8 * dc);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const int item = it ? (lane < 8 ? lane + 64 : lane) : lane;   // items 64..71 on lanes 0..7
-    const int n = item >> 2;
-    a.pr[it] = item & 3;
-    a.ny[it] = n / 6;
-    a.nx[it] = n - 6 * a.ny[it];
-  }
-  return a;
+template <int GDT>
+__device__ __forceinline__ GridRaw<GDT> grid_row_load(const GridCols<GDT>& c, int r) {
+  GridRaw<GDT> o;
+  const size_t at = (size_t)(uint32_t)r * c.row;
+  o.v[0] = gload<uint32_t>(c.k0 + at, c.o0);
+  o.v[1] = gload<uint32_t>(c.k0 + at, c.o1);
+  o.v[2] = gload<uint32_t>(c.k1 + at, c.o0);
+  o.v[3] = gload<uint32_t>(c.k1 + at, c.o1);
+  return o;
 }
-
-// Global loads of the pass at texel (x0, y0): this lane's BC4 block and its grid window items
-// of both keys (node window from grid node (x0/4 - 1, y0/4 - 1), clamped to the grid).
-__device__ __forceinline__ void tile_issue(const TileAddr& a, int x0, int y0, TileLoads& t) {
-  const uint32_t bi = (uint32_t)((y0 >> 2) * a.wb + (x0 >> 2)) * 64u + a.boff;
-  const unsigned long long bw = gload<unsigned long long>(a.bc4, bi);
-  t.blk = make_uint2((uint32_t)bw, (uint32_t)(bw >> 32));
-  const int gx0 = (x0 >> 2) - 1, gy0 = (y0 >> 2) - 1;
+template <>
+__device__ __forceinline__ GridRaw<NDGI_DTYPE_F32> grid_row_load(const GridCols<NDGI_DTYPE_F32>& c, int r) {
+  GridRaw<NDGI_DTYPE_F32> o;
+  const size_t at = (size_t)(uint32_t)r * c.row;
 #pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const int gx = min(max(gx0 + a.nx[it], 0), a.gw1), gy = min(max(gy0 + a.ny[it], 0), a.gh1);
-    const uint32_t off = (((uint32_t)__umul24(gy, a.gw) + (uint32_t)gx) * 4u + (uint32_t)a.pr[it]) * 4u;
-    t.g0[it] = gload<uint32_t>(a.g0, off);
-    t.g1[it] = gload<uint32_t>(a.g1, off);
+  for (int i = 0; i < 4; ++i) {
+    const unsigned long long b = gload<unsigned long long>((i & 2 ? c.k1 : c.k0) + at, i & 1 ? c.o1 : c.o0);
+    o.v[i] = make_float2(__uint_as_float((uint32_t)b), __uint_as_float((uint32_t)(b >> 32)));
   }
+  return o;
 }
 
 __device__ __forceinline__ float2 half2_bits(uint32_t w) {
   return make_float2((float)__builtin_bit_cast(_Float16, (uint16_t)(w & 0xffffu)),
                      (float)__builtin_bit_cast(_Float16, (uint16_t)(w >> 16)));
 }
+__device__ __forceinline__ float2 half2_bits(float2 v) { return v; }
 
-// FP16-grid tile path over one sub-tile.  Passes run row-slab by column-slab; the loads of
-// pass p+1 are in flight while pass p computes.
-__device__ __forceinline__ void tile_subtile(const Dec16& dec, const ndgi_model& m, const ndgi_page_req& rq,
-                                             const Keys& k, int page, int ox, int oy, int tw, int th, void* dst,
-                                             int64_t pitch, int lane, TileLds& L) {
-  const int g = lane >> 4, j = lane & 15;
-  // grid corner of this lane's column in the node window, and its weight (x % 4 = j % 4)
-  const int cx = ((2 * j - 3) >> 3) + 1;
-  const float wx1 = (float)((2 * j - 3) & 7) * 0.125f, wx0 = 1.0f - wx1;
-  // decode role: footprint db, channel dc, row pair drp
-  const int db = lane >> 4, dc = (lane >> 1) & 7, drp = lane & 1;
-  const uint8_t* sp8 = (const uint8_t*)L.sp;
-  const int bx = page * rq.page_x + ox, by = page * rq.page_y + oy;
-  const int np = tw * th;
-  const TileAddr ta = tile_addr(m, k, lane, db, dc);
-  // this lane's output texel (row g, column j) of the sub-tile's first pass; later passes add
-  // a uniform offset
-  _Float16* const out0 = (_Float16*)dst + (rq.dst_offset + (int64_t)(oy + g) * pitch + (ox + j)) * 3;
-  TileLoads cur;
-  tile_issue(ta, bx, by, cur);
-  for (int p = 0; p < np; ++p) {
-    const int a = p % tw, b = p / tw;
-    // stage this pass: time-blend the grid window, decode the BC4 rows
+template <int GDT>
+__device__ __forceinline__ float2 grid_row_sample(const GridCols<GDT>& c, const GridRaw<GDT>& r) {
+  float2 o = make_float2(0.0f, 0.0f);
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      if (it == 0 || lane < 8) {
-        const float2 v0 = half2_bits(cur.g0[it]), v1 = half2_bits(cur.g1[it]);
-        // w0 v0 as an FMA with a zero addend: one mixed-precision FMA on the FP16 word (the
-        // same rounded product)
-        L.gt[it ? lane + 64 : lane] =
-            make_float2(fmaf(k.w1, v1.x, fmaf(k.w0, v0.x, 0.0f)), fmaf(k.w1, v1.y, fmaf(k.w0, v0.y, 0.0f)));
-      }
-    }
-    uint32_t row0, row1;
-    bc4_rows(cur.blk.x, cur.blk.y, drp, row0, row1);
-    L.sp[dc * 20 + (2 * drp) * 4 + db] = row0;
-    L.sp[dc * 20 + (2 * drp + 1) * 4 + db] = row1;
-    if (p + 1 < np) {
-      const int a1 = (p + 1) % tw, b1 = (p + 1) / tw;
-      tile_issue(ta, bx + 16 * a1, by + 4 * b1, cur);
-    }
-    wave_sync();
-    f4v acc = dec.c3;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t sa = sp8[(2 * g) * 80 + q * 16 + j];
-      const uint32_t sb = sp8[(2 * g + 1) * 80 + q * 16 + j];
-      const uint32_t spair = sa | (sb << 16) | 0x64006400u;
-      const int cy = ((2 * q - 3) >> 3) + 1;
-      const float wy1 = (float)((2 * q - 3) & 7) * 0.125f, wy0 = 1.0f - wy1;
-      const float2 c00 = L.gt[(cy * 6 + cx) * 4 + g], c01 = L.gt[(cy * 6 + cx + 1) * 4 + g];
-      const float2 c10 = L.gt[((cy + 1) * 6 + cx) * 4 + g], c11 = L.gt[((cy + 1) * 6 + cx + 1) * 4 + g];
-      const float ga = wy0 * fmaf(wx1, c01.x, wx0 * c00.x) + wy1 * fmaf(wx1, c11.x, wx0 * c10.x);
-      const float gb = wy0 * fmaf(wx1, c01.y, wx0 * c00.y) + wy1 * fmaf(wx1, c11.y, wx0 * c10.y);
-      dec16_group(dec, texel_x(spair, ga, gb), q, acc);
-    }
-    wave_sync();
-    store_rgb<NDGI_PREC_F16>(out0 + ((int64_t)(4 * b) * pitch + 16 * a) * 3, 0, acc, false);
+  for (int i = 0; i < 4; ++i) {   // the first term as an FMA with a zero addend: the same rounded product
+    const float2 v = half2_bits(r.v[i]);
+    o.x = fmaf(c.w[i], v.x, o.x);
+    o.y = fmaf(c.w[i], v.y, o.y);
   }
+  return o;
 }
 
-// Decode one (16*tw) x (4*th) sub-tile of a page; a pass covers 16 columns x 4 rows and
-// group q of the pass is row q.
+// One sub-tile.  R4: the grid is a quarter of the texel resolution, where a pass's rows lie at
+// fixed places between three grid rows; otherwise each texel row's grid rows and weight come
+// from texel_axis, 64 rows at a time (one a lane), and the two row samples move on as they do.
 template <int PREC, int GDT, bool R4>
 __device__ __forceinline__ void page_subtile(const Dec<PREC>& dec, const ndgi_model& m, const ndgi_page_req& rq,
                                              const Keys& k, int page, int ox, int oy, int tw, int th, void* dst,
-                                             int64_t pitch, int lane) {
+                                             int64_t pitch, int lane, PageLds& L) {
+  typedef typename std::conditional<PREC == NDGI_PREC_F16, _Float16, float>::type OutT;
   const int g = lane >> 4, j = lane & 15;
-  const int bx = page * rq.page_x, by = page * rq.page_y;
-  for (int b = 0; b < th; ++b) {
-    for (int a = 0; a < tw; ++a) {
-      f4v acc = dec.bias3();
+  const uint8_t* const sp8 = (const uint8_t*)L.sp;
+  const int by = page * rq.page_y + oy;
+  const uint32_t wb = (uint32_t)m.W >> 2;
+  const int bf = lane >> 3, bc = lane & 7;   // this lane's footprint (pass bf >> 2, column bf & 3) and channel
+  GridCols<GDT> gc;
+  gc.row = (uint32_t)m.Gw * GridCols<GDT>::kNode;
+  const size_t plane = (size_t)m.Gh * gc.row;
+  gc.k0 = (gbyte_ptr)m.grid + (size_t)k.k0 * plane;
+  gc.k1 = (gbyte_ptr)m.grid + (size_t)k.k1 * plane;
+#pragma unroll 1
+  for (int a = 0; a < tw; ++a) {
+    const int bx = page * rq.page_x + ox + 16 * a;
+    // this lane's column in the grid
+    {
+      const Axis cx = texel_axis<R4>(bx + j, m.Gw, m.W);
+      gc.o0 = (uint32_t)cx.i0 * GridCols<GDT>::kNode + (uint32_t)g * (GridCols<GDT>::kNode / 4);
+      gc.o1 = (uint32_t)cx.i1 * GridCols<GDT>::kNode + (uint32_t)g * (GridCols<GDT>::kNode / 4);
+      gc.w[0] = k.w0 * cx.w0;
+      gc.w[1] = k.w0 * cx.w1;
+      gc.w[2] = k.w1 * cx.w0;
+      gc.w[3] = k.w1 * cx.w1;
+    }
+    // blocks of the pass pair at rows 8 pr (the last pass again past an odd end)
+    const gbyte_ptr blocks = (gbyte_ptr)m.bc4 + ((size_t)((uint32_t)by >> 2) * wb + ((uint32_t)bx >> 2)) * 64u;
+    auto load_blocks = [&](int b) {
+      const uint32_t row = (uint32_t)min(b + (bf >> 2), th - 1);
+      return gload<unsigned long long>(blocks, (row * wb + (uint32_t)(bf & 3)) * 64u + 8u * (uint32_t)bc);
+    };
+    unsigned long long blk = load_blocks(0);
+    // grid rows: lo and hi bound the current texel rows, nx is the row after, in flight
+    int r_lo, r_hi, rows_packed = 0;
+    float rows_w1 = 0.0f;
+    auto row_axes = [&](int r0) {   // texel rows r0 .. r0 + 63 of the slab, one a lane
+      const Axis ry = texel_axis<false>(min(by + r0 + lane, m.H - 1), m.Gh, m.H);
+      rows_packed = ry.i0 | (ry.i1 << 16);
+      rows_w1 = ry.w1;
+    };
+    if constexpr (R4) {
+      r_lo = max((by >> 2) - 1, 0);
+      r_hi = by >> 2;
+    } else {
+      row_axes(0);
+      const int p = __builtin_amdgcn_readlane(rows_packed, 0);
+      r_lo = p & 0xffff;
+      r_hi = p >> 16;
+    }
+    float2 lo, hi;
+    GridRaw<GDT> nx;
+    {
+      const GridRaw<GDT> l0 = grid_row_load<GDT>(gc, r_lo), h0 = grid_row_load<GDT>(gc, r_hi);
+      nx = grid_row_load<GDT>(gc, min(r_hi + 1, m.Gh - 1));
+      lo = grid_row_sample<GDT>(gc, l0);
+      hi = grid_row_sample<GDT>(gc, h0);
+    }
+    OutT* out = (OutT*)dst + (rq.dst_offset + (int64_t)(oy + g) * pitch + (ox + 16 * a + j)) * 3;
+#pragma unroll 1
+    for (int b = 0; b < th; ++b) {
+      if (!(b & 1)) {
+        uint32_t r[4];
+        bc4_rows4((uint32_t)blk, (uint32_t)(blk >> 32), r);
+        uint32_t* const w = &L.sp[bf >> 2][bc * 20 + (bf & 3)];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float f[4];
-        texel_inputs<GDT, R4>(m, bx + ox + 16 * a + j, by + oy + 4 * b + q, k, g, f);
-        dec.group(f, q, acc);
+        for (int i = 0; i < 4; ++i) w[4 * i] = r[i];
+        if (b + 2 < th) blk = load_blocks(b + 2);
+        wave_sync();
       }
-      // lane (g, j) holds the texel of row g of this pass
-      const int64_t di = rq.dst_offset + (int64_t)(oy + 4 * b + g) * pitch + (ox + 16 * a + j);
-      store_rgb<PREC>(dst, (size_t)di, acc, false);
+      const uint8_t* const at = sp8 + (b & 1) * 640 + (2 * g) * 80 + j;
+      typename Dec<PREC>::Acc acc = dec.start();
+      if constexpr (R4) {
+        const float2 nw = grid_row_sample<GDT>(gc, nx);
+        nx = grid_row_load<GDT>(gc, min((by >> 2) + b + 2, m.Gh - 1));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float w1 = (float)((2 * q - 3) & 7) * 0.125f, w0 = 1.0f - w1;   // texel rows 4n + q
+          const float2 s = q < 2 ? lo : hi, e = q < 2 ? hi : nw;
+          dec.texel_group(at[16 * q], at[80 + 16 * q], fmaf(w1, e.x, w0 * s.x), fmaf(w1, e.y, w0 * s.y), q, acc);
+        }
+        lo = hi;
+        hi = nw;
+      } else {
+        if (b > 0 && !(b & 15)) row_axes(4 * b);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int rl = (4 * b + q) & 63;
+          const int p = __builtin_amdgcn_readlane(rows_packed, rl), i0 = p & 0xffff, i1 = p >> 16;
+          const float w1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rows_w1), rl)), w0 = 1.0f - w1;
+          if (i0 != r_lo || i1 != r_hi) {   // uniform
+            if (i0 == r_hi && i1 == min(r_hi + 1, m.Gh - 1)) {   // on by one row: the one in flight
+              lo = hi;
+              hi = grid_row_sample<GDT>(gc, nx);
+            } else {
+              const GridRaw<GDT> l0 = grid_row_load<GDT>(gc, i0), h0 = grid_row_load<GDT>(gc, i1);
+              lo = grid_row_sample<GDT>(gc, l0);
+              hi = grid_row_sample<GDT>(gc, h0);
+            }
+            r_lo = i0;
+            r_hi = i1;
+            nx = grid_row_load<GDT>(gc, min(r_hi + 1, m.Gh - 1));
+          }
+          dec.texel_group(at[16 * q], at[80 + 16 * q], fmaf(w1, hi.x, w0 * lo.x), fmaf(w1, hi.y, w0 * lo.y), q, acc);
+        }
+      }
+      if ((b & 1) || b + 1 == th) wave_sync();   // every lane has read the pair's bytes
+      store_rgb<PREC>(out, 0, dec.finish(acc), false);
+      out += 12 * pitch;
     }
   }
 }
 
-// Maps the FP16 tile kernel serves: grid at a quarter of the texel resolution, FP16 grid
-// and decoder.
-__device__ __forceinline__ bool tile_eligible(const ndgi_model& m) {
-  return m.W == 4 * m.Gw && m.H == 4 * m.Gh && m.grid_dtype == NDGI_DTYPE_F16 && m.mlp_dtype == NDGI_DTYPE_F16;
-}
-
-// Request scan shared by the two page kernels: item `it` -> request, sub-tile, model.
-// Returns false (and flags the request once) when the request is invalid.
+// Request of item `it`: its sub-tile s and its model.  Returns false (and flags the request
+// once) when the request is invalid.
 struct PageItem {
   ndgi_page_req rq;
   int s;
@@ -283,7 +317,7 @@ struct PageItem {
 __device__ __forceinline__ bool page_item(const ndgi_model* __restrict__ models, int32_t n_models,
                                           const ndgi_page_req* __restrict__ reqs, int64_t it, int64_t per_req,
                                           int page, int lane, int& cur, ndgi_model& m, PageItem& pi,
-                                          uint32_t* __restrict__ flags, bool report) {
+                                          uint32_t* __restrict__ flags) {
   const int r = (int)(it / per_req);
   pi.s = (int)(it - (int64_t)r * per_req);
   pi.rq = reqs[r];
@@ -294,17 +328,19 @@ __device__ __forceinline__ bool page_item(const ndgi_model* __restrict__ models,
     cur = rq.model;
   }
   ok = ok && (int64_t)page * (rq.page_x + 1) <= m.W && (int64_t)page * (rq.page_y + 1) <= m.H;
-  if (!ok && report && lane == 0 && pi.s == 0) atomicOr(flags, NDGI_FLAG_BAD_PAGE_REQUEST);
+  if (!ok && lane == 0 && pi.s == 0) atomicOr(flags, NDGI_FLAG_BAD_PAGE_REQUEST);
   return ok;
 }
 
-// FP16 requests on tile-eligible maps (tile path).
-__global__ __launch_bounds__(256) void k_decode_tiles(const ndgi_model* __restrict__ models, int32_t n_models,
+template <int PREC>
+__global__ __launch_bounds__(256, 3) void k_decode_pages(const ndgi_model* __restrict__ models, int32_t n_models,
                                                       const ndgi_page_req* __restrict__ reqs,
                                                       const int32_t* __restrict__ n_reqs_dev, int32_t max_reqs,
                                                       int32_t page, void* __restrict__ dst, int64_t pitch, int tw,
                                                       int th, uint32_t* __restrict__ flags) {
+  __shared__ PageLds lds[4];
   const int lane = threadIdx.x & 63;
+  PageLds& L = lds[threadIdx.x >> 6];
   int n_req = *n_reqs_dev;
   n_req = n_req < 0 ? 0 : (n_req > max_reqs ? max_reqs : n_req);
   const int sub_w = 16 * tw, sub_h = 4 * th;
@@ -312,63 +348,26 @@ __global__ __launch_bounds__(256) void k_decode_tiles(const ndgi_model* __restri
   const int64_t per_req = (int64_t)nsx * nsy;
   const int64_t total = (int64_t)n_req * per_req;
   const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
-  const int64_t wave0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
-  __shared__ TileLds tlds[4];
-  Dec16 dec;
-  int dmodel = -1, cur = -1;
-  ndgi_model m = {};
-  PageItem pi;
-  for (int64_t it = wave0; it < total; it += nwaves) {
-    if (!page_item(models, n_models, reqs, it, per_req, page, lane, cur, m, pi, flags, true)) continue;
-    if (!tile_eligible(m)) continue;                            // served by the general kernel
-    if (dmodel != pi.rq.model) {
-      load_dec16<NDGI_DTYPE_F16, true>(dec, m.mlp, lane);
-      dmodel = pi.rq.model;
-    }
-    const Keys k = make_keys(pi.rq.t, m.T);
-    const int ox = (pi.s % nsx) * sub_w, oy = (pi.s / nsx) * sub_h;
-    tile_subtile(dec, m, pi.rq, k, page, ox, oy, tw, th, dst, pitch, lane, tlds[threadIdx.x >> 6]);
-  }
-}
-
-// General page decode (any grid ratio, either precision).  With SKIP_TILES the requests the
-// tile kernel serves are skipped.
-template <int PREC, bool SKIP_TILES>
-__global__ __launch_bounds__(256) void k_decode_pages(const ndgi_model* __restrict__ models, int32_t n_models,
-                                                      const ndgi_page_req* __restrict__ reqs,
-                                                      const int32_t* __restrict__ n_reqs_dev, int32_t max_reqs,
-                                                      int32_t page, void* __restrict__ dst, int64_t pitch, int tw,
-                                                      int th, uint32_t* __restrict__ flags) {
-  const int lane = threadIdx.x & 63;
-  int n_req = *n_reqs_dev;
-  n_req = n_req < 0 ? 0 : (n_req > max_reqs ? max_reqs : n_req);
-  const int sub_w = 16 * tw, sub_h = 4 * th;
-  const int nsx = page / sub_w, nsy = page / sub_h;
-  const int64_t per_req = (int64_t)nsx * nsy;
-  const int64_t total = (int64_t)n_req * per_req;
-  const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
-  const int64_t wave0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
+  const int64_t wave0 = uniform((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
   Dec<PREC> dec;
   int dmodel = -1, cur = -1;
   ndgi_model m = {};
   PageItem pi;
   for (int64_t it = wave0; it < total; it += nwaves) {
-    // the tile kernel already reported invalid requests when it runs
-    if (!page_item(models, n_models, reqs, it, per_req, page, lane, cur, m, pi, flags, !SKIP_TILES)) continue;
-    const bool r4 = m.W == 4 * m.Gw && m.H == 4 * m.Gh;
-    if (SKIP_TILES && tile_eligible(m)) continue;
+    if (!page_item(models, n_models, reqs, it, per_req, page, lane, cur, m, pi, flags)) continue;
     if (dmodel != pi.rq.model) {
-      dec.load(m.mlp, m.mlp_dtype, lane);
+      dec.load_texel(m.mlp, m.mlp_dtype, lane);
       dmodel = pi.rq.model;
     }
     const Keys k = make_keys(pi.rq.t, m.T);
     const int ox = (pi.s % nsx) * sub_w, oy = (pi.s / nsx) * sub_h;
+    const bool r4 = m.W == 4 * m.Gw && m.H == 4 * m.Gh;
     if (m.grid_dtype == NDGI_DTYPE_F16) {
-      if (r4) page_subtile<PREC, NDGI_DTYPE_F16, true>(dec, m, pi.rq, k, page, ox, oy, tw, th, dst, pitch, lane);
-      else page_subtile<PREC, NDGI_DTYPE_F16, false>(dec, m, pi.rq, k, page, ox, oy, tw, th, dst, pitch, lane);
+      if (r4) page_subtile<PREC, NDGI_DTYPE_F16, true>(dec, m, pi.rq, k, page, ox, oy, tw, th, dst, pitch, lane, L);
+      else page_subtile<PREC, NDGI_DTYPE_F16, false>(dec, m, pi.rq, k, page, ox, oy, tw, th, dst, pitch, lane, L);
     } else {
-      if (r4) page_subtile<PREC, NDGI_DTYPE_F32, true>(dec, m, pi.rq, k, page, ox, oy, tw, th, dst, pitch, lane);
-      else page_subtile<PREC, NDGI_DTYPE_F32, false>(dec, m, pi.rq, k, page, ox, oy, tw, th, dst, pitch, lane);
+      if (r4) page_subtile<PREC, NDGI_DTYPE_F32, true>(dec, m, pi.rq, k, page, ox, oy, tw, th, dst, pitch, lane, L);
+      else page_subtile<PREC, NDGI_DTYPE_F32, false>(dec, m, pi.rq, k, page, ox, oy, tw, th, dst, pitch, lane, L);
     }
   }
 }
@@ -376,19 +375,13 @@ __global__ __launch_bounds__(256) void k_decode_pages(const ndgi_model* __restri
 int launch_pages(ndgi_ctx* ctx, const ndgi_model* models, int32_t n_models, const ndgi_page_req* reqs,
                  const int32_t* n_reqs, int32_t max_reqs, int32_t page, void* dst, int64_t pitch, int prec,
                  hipStream_t s) {
-  if (prec == NDGI_PREC_F16) {
-    hipLaunchKernelGGL(k_decode_tiles, dim3(resident_wgs(ctx, (const void*)k_decode_tiles)), dim3(256), 0, s, models,
-                       n_models, reqs, n_reqs, max_reqs, page, dst, pitch, ctx->tile_w, ctx->tile_h, ctx->flags_dev);
-    hipLaunchKernelGGL((k_decode_pages<NDGI_PREC_F16, true>),
-                       dim3(resident_wgs(ctx, (const void*)k_decode_pages<NDGI_PREC_F16, true>)), dim3(256), 0, s,
-                       models, n_models, reqs, n_reqs, max_reqs, page, dst, pitch, ctx->tile_w, ctx->tile_h,
-                       ctx->flags_dev);
-  } else {
-    hipLaunchKernelGGL((k_decode_pages<NDGI_PREC_F32, false>),
-                       dim3(resident_wgs(ctx, (const void*)k_decode_pages<NDGI_PREC_F32, false>)), dim3(256), 0, s,
-                       models, n_models, reqs, n_reqs, max_reqs, page, dst, pitch, ctx->tile_w, ctx->tile_h,
-                       ctx->flags_dev);
-  }
+#define NDGI_PAGES(P)                                                                                             \
+  hipLaunchKernelGGL(k_decode_pages<P>, dim3(resident_wgs(ctx, (const void*)k_decode_pages<P>)), dim3(256), 0, s, \
+                     models, n_models, reqs, n_reqs, max_reqs, page, dst, pitch, ctx->tile_w, ctx->tile_h,        \
+                     ctx->flags_dev)
+  if (prec == NDGI_PREC_F16) NDGI_PAGES(NDGI_PREC_F16);
+  else NDGI_PAGES(NDGI_PREC_F32);
+#undef NDGI_PAGES
   NDGI_HIP(hipGetLastError());
   return NDGI_OK;
 }

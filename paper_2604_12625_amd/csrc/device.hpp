@@ -85,13 +85,12 @@ __device__ __forceinline__ float bc4_texel_f(uint32_t lo, uint32_t hi, uint32_t 
   return v;
 }
 
-// Rows 2rp and 2rp+1 of a BC4 block (lo = bytes 0..3, hi = bytes 4..7) as 4 bytes each.
-// The 8-entry palette is built once: the interior entries are 1024 + e0 + 0.5 + j*(e1-e0)/D
-// rounded toward zero to FP16 (integers are exact in [1024, 2048)), which equals the
-// palette's round-to-nearest value since the exact quotient is never within 0.5/D of an
-// integer.  The row's four 3-bit selectors are spread into a byte selector and one
-// v_perm_b32 picks four texels from the palette.
-__device__ __forceinline__ void bc4_rows(uint32_t lo, uint32_t hi, int rp, uint32_t& r0, uint32_t& r1) {
+// The 8-entry palette of a BC4 block (lo = bytes 0..3, hi = bytes 4..7) as bytes:
+// [e0, e1, p1, p2 | p3, p4, p5, p6] or, in 6-value mode, [.. | p3, p4, 0, 255].  The interior
+// entries are 1024 + e0 + 0.5 + j*(e1-e0)/D rounded toward zero to FP16 (integers are exact in
+// [1024, 2048)), which equals the palette's round-to-nearest value since the exact quotient is
+// never within 0.5/D of an integer.
+__device__ __forceinline__ uint2 bc4_palette_bytes(uint32_t lo) {
   const uint32_t ie0 = lo & 0xffu, ie1 = (lo >> 8) & 0xffu;
   const bool eight = ie0 > ie1;
   const float e0 = (float)ie0, e1 = (float)ie1;
@@ -100,20 +99,31 @@ __device__ __forceinline__ void bc4_rows(uint32_t lo, uint32_t hi, int rp, uint3
   const uint32_t p12 = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(fmaf(1.0f, B, A), fmaf(2.0f, B, A)));
   const uint32_t p34 = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(fmaf(3.0f, B, A), fmaf(4.0f, B, A)));
   const uint32_t p56 = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(fmaf(5.0f, B, A), fmaf(6.0f, B, A)));
-  // palette bytes: [e0, e1, p1, p2 | p3, p4, p5, p6] or, in 6-value mode, [.. | p3, p4, 0, 255]
-  const uint32_t pal_lo = __builtin_amdgcn_perm(p12, lo, 0x06040100u);
-  const uint32_t pal_hi = __builtin_amdgcn_perm(p56, p34, eight ? 0x06040200u : 0x0D0C0200u);
-  const uint64_t bits = (((uint64_t)hi << 32) | lo) >> (16 + 24 * rp);
-  const uint32_t c24 = (uint32_t)bits;
-#pragma unroll
-  for (int rr = 0; rr < 2; ++rr) {
-    const uint32_t c = (c24 >> (12 * rr)) & 0xfffu;    // four 3-bit selectors
-    uint32_t t = (c | (c << 10)) & 0x003f003fu;
-    t = (t | (t << 5)) & 0x07070707u;                  // one selector per byte
-    const uint32_t v = __builtin_amdgcn_perm(pal_hi, pal_lo, t);
-    if (rr == 0) r0 = v;
-    else r1 = v;
-  }
+  return make_uint2(__builtin_amdgcn_perm(p12, lo, 0x06040100u),
+                    __builtin_amdgcn_perm(p56, p34, eight ? 0x06040200u : 0x0D0C0200u));
+}
+// Four texels of a row from its four 3-bit selectors c (12 bits): the selectors are spread into
+// a byte selector and one v_perm_b32 picks the palette's bytes.
+__device__ __forceinline__ uint32_t bc4_pick(uint2 pal, uint32_t c) {
+  uint32_t t = (c | (c << 10)) & 0x003f003fu;
+  t = (t | (t << 5)) & 0x07070707u;
+  return __builtin_amdgcn_perm(pal.y, pal.x, t);
+}
+// Rows 2rp and 2rp+1 of a block as 4 bytes each.
+__device__ __forceinline__ void bc4_rows(uint32_t lo, uint32_t hi, int rp, uint32_t& r0, uint32_t& r1) {
+  const uint2 pal = bc4_palette_bytes(lo);
+  const uint32_t c24 = (uint32_t)((((uint64_t)hi << 32) | lo) >> (16 + 24 * rp));
+  r0 = bc4_pick(pal, c24 & 0xfffu);
+  r1 = bc4_pick(pal, (c24 >> 12) & 0xfffu);
+}
+// All four rows of a block.
+__device__ __forceinline__ void bc4_rows4(uint32_t lo, uint32_t hi, uint32_t r[4]) {
+  const uint2 pal = bc4_palette_bytes(lo);
+  const uint32_t c01 = __builtin_amdgcn_alignbit(hi, lo, 16), c23 = hi >> 8;   // selectors of rows 0, 1 and 2, 3
+  r[0] = bc4_pick(pal, c01 & 0xfffu);
+  r[1] = bc4_pick(pal, (c01 >> 12) & 0xfffu);
+  r[2] = bc4_pick(pal, c23 & 0xfffu);
+  r[3] = bc4_pick(pal, c23 >> 12);
 }
 
 // ------------------------------------------------------------------ sampling helpers
@@ -197,63 +207,15 @@ __device__ __forceinline__ Keys make_keys(float t, int T) {
   return k;
 }
 
-// Grid channels (2p, 2p+1) of node `node` ([T][Gh][Gw] flattened), 8 channels per node.
-template <int GDT>
-__device__ __forceinline__ float2 grid_pair(const void* grid, size_t node, int p) {
-  if constexpr (GDT == NDGI_DTYPE_F16) {
-    const uint32_t w = ((const uint32_t*)grid)[node * 4 + p];
-    const _Float16 lo = __builtin_bit_cast(_Float16, (uint16_t)(w & 0xffffu));
-    const _Float16 hi = __builtin_bit_cast(_Float16, (uint16_t)(w >> 16));
-    return make_float2((float)lo, (float)hi);
-  }
-  return ((const float2*)grid)[node * 4 + p];
-}
-
-// Grid sample of channels 2g, 2g+1: bilinear in space on the node axes, linear in time.
-template <int GDT>
-__device__ __forceinline__ float2 grid_sample(const ndgi_model& m, const Axis& ax, const Axis& ay, const Keys& k,
-                                              int g) {
-  float a = 0.0f, b = 0.0f;
-#pragma unroll
-  for (int tk = 0; tk < 2; ++tk) {
-    const int key = tk ? k.k1 : k.k0;
-    const float wt = tk ? k.w1 : k.w0;
-#pragma unroll
-    for (int yy = 0; yy < 2; ++yy) {
-      const int gy = yy ? ay.i1 : ay.i0;
-      const float wy = wt * (yy ? ay.w1 : ay.w0);
-      const size_t row = ((size_t)key * m.Gh + gy) * m.Gw;
-#pragma unroll
-      for (int xx = 0; xx < 2; ++xx) {
-        const int gx = xx ? ax.i1 : ax.i0;
-        const float w = wy * (xx ? ax.w1 : ax.w0);
-        const float2 v = grid_pair<GDT>(m.grid, row + gx, g);
-        a = fmaf(w, v.x, a);
-        b = fmaf(w, v.y, b);
-      }
-    }
-  }
-  return make_float2(a, b);
-}
-
-// Spatial channels 2g, 2g+1 of texel (x, y) as integers 0..255.
-__device__ __forceinline__ uint2 spatial_pair(const ndgi_model& m, int x, int y, int g) {
-  const uint4 b = *(const uint4*)(m.bc4 + ((size_t)(y >> 2) * (m.W >> 2) + (x >> 2)) * 64 + 16 * g);
-  const uint32_t slot = 4u * (uint32_t)(y & 3) + (uint32_t)(x & 3);
-  return make_uint2(bc4_texel(b.x, b.y, slot), bc4_texel(b.z, b.w, slot));
-}
-
 // ------------------------------------------------------- explicit-query features
 // The decode of explicit (u, v, t) queries runs in two phases per wave pass of 64
 // queries.  Phase A: lane l computes all 16 decoder inputs of query l in FP32 (x[0..7]
-// spatial, x[8..15] grid) and writes them to a wave-private LDS block.  Phase B: the MFMA
-// decoder reads them back in its operand layout (lane (g, j) of group q takes inputs
-// 2g, 2g+1 and 8+2g, 8+2g+1 of query 16q + j).  Address and weight arithmetic is thus done
+// spatial, x[8..15] grid).  Phase B: after a handoff in registers the MFMA decoder has them
+// in its operand layout (lane (g, j) of group q takes inputs 2g, 2g+1 and 8+2g, 8+2g+1 of
+// query 16q + j).  Address and weight arithmetic is thus done
 // once per query instead of once per lane group.  Every explicit-query decode uses these
 // helpers, with the bilinear taps summed in the order (y0,x0), (y0,x1), (y1,x0), (y1,x1)
 // and the keys k0 then k1, so that they agree bit for bit.
-
-constexpr int kFeatStride = 20;   // floats per query row of the LDS block (80 B: 16-B aligned)
 
 // Bilinear weights of the four taps, in summation order.
 __device__ __forceinline__ void tap_weights(const Axis& ax, const Axis& ay, float w[4]) {
@@ -405,27 +367,6 @@ __device__ __forceinline__ void transpose_chunks(const float sp[8], const float 
   transpose_rows(r);
 }
 
-// Phase A store: this lane's 16 inputs into its row of the wave's block.
-__device__ __forceinline__ void store_feats(float* feat, int lane, const float s[8], const float gr[8]) {
-  float4* r = (float4*)(feat + lane * kFeatStride);
-  r[0] = make_float4(s[0], s[1], s[2], s[3]);
-  r[1] = make_float4(s[4], s[5], s[6], s[7]);
-  r[2] = make_float4(gr[0], gr[1], gr[2], gr[3]);
-  r[3] = make_float4(gr[4], gr[5], gr[6], gr[7]);
-}
-
-// Lane inputs at the centre of texel (x, y) (page / frame decode): the spatial sample is
-// the texel itself; the grid axes come from texel_axis.
-template <int GDT, bool R4>
-__device__ __forceinline__ void texel_inputs(const ndgi_model& m, int x, int y, const Keys& k, int g, float f[4]) {
-  const uint2 s = spatial_pair(m, x, y, g);
-  const float2 gv = grid_sample<GDT>(m, texel_axis<R4>(x, m.Gw, m.W), texel_axis<R4>(y, m.Gh, m.H), k, g);
-  f[0] = (float)s.x * (1.0f / 255.0f);
-  f[1] = (float)s.y * (1.0f / 255.0f);
-  f[2] = gv.x;
-  f[3] = gv.y;
-}
-
 // ------------------------------------------------------------------ FP16 MFMA decoder
 // Every FP16 operand that is not stored data (decoder inputs, hidden activations) is fed
 // as a compensated pair v = hi + lo with lo = fp16(v - hi), so the products see about 22
@@ -516,6 +457,7 @@ struct Dec16 {
 template <int MDT, bool TEXEL>
 __device__ __forceinline__ void load_dec16(Dec16& d, const void* mlp, int lane) {
   const int g = lane >> 4, i = lane & 15;
+  float off[2] = {0.0f, 0.0f};   // TEXEL: sum over the spatial inputs of unit 16mc + i, in every group
 #pragma unroll
   for (int mc = 0; mc < 2; ++mc) {
     const int u = 16 * mc + i;
@@ -534,20 +476,16 @@ __device__ __forceinline__ void load_dec16(Dec16& d, const void* mlp, int lane) 
 #pragma unroll
     for (int e = 0; e < 8; ++e)
       d.a2[mc][e] = (_Float16)ld<MDT>(mlp, kOffW2 + u * 32 + unit_of(g, e));
+    if (TEXEL) {   // each group holds two of the eight inputs
+      float s = ((float)d.a1[mc][0] + (float)d.a1[mc][4]) + ((float)d.a1[mc][1] + (float)d.a1[mc][5]);
+      s += __shfl_xor(s, 16, 64);
+      off[mc] = s + __shfl_xor(s, 32, 64);
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int ur = 16 * mc + 4 * g + r;
       float b = ld<MDT>(mlp, kOffB1 + ur);
-      if (TEXEL) {
-        float off = 0.0f;
-#pragma unroll
-        for (int sc = 0; sc < 8; ++sc) {
-          const float ws = ld<MDT>(mlp, kOffW1 + ur * 16 + sc) * (1.0f / 255.0f);
-          const _Float16 hi = (_Float16)ws;
-          off += (float)hi + (float)(_Float16)(ws - (float)hi);
-        }
-        b -= 1024.0f * off;
-      }
+      if (TEXEL) b -= 1024.0f * __shfl(off[mc], 4 * g + r, 64);
       d.c1[mc][r] = b;
       d.c2[mc][r] = ld<MDT>(mlp, kOffB2 + ur);
     }
@@ -585,12 +523,16 @@ __device__ __forceinline__ void dec16_group(const Dec16& d, const h8v& x, int q,
 // ------------------------------------------------------------------ FP32 MFMA decoder
 // v_mfma_f32_16x16x4_f32: lane (g, i) supplies one K element (k = g); layer K depths 16
 // and 32 are covered by 4 and 8 chained MFMAs, step m taking element m of the lane's
-// share (input_of(g, m) in layer 1, unit_of(g, m) in layers 2-3).
+// share (input_of(g, m) in layer 1, unit_of(g, m) in layer 2).  The output layer has three
+// rows: on MFMA it would use 3 of 16 rows at 8 instructions a group (a quarter of the decoder's
+// matrix time, which bounds this path).  Instead each lane multiplies its own eight units into
+// three partial sums per group with FMAs, and the four lane groups' sums are added in
+// registers, group q's into lane group q (see finish).
 struct Dec32 {
   float a1[2][4];
   float a2[2][8];
-  float a3[4][8];
-  f4v c1[2], c2[2], c3;
+  float w3[3][8];         // W3 rows at units unit_of(g, 0..7)
+  f4v c1[2], c2[2], c3;   // c3: the output bias (the same in every lane)
 };
 
 template <int MDT>
@@ -608,18 +550,15 @@ __device__ __forceinline__ void load_dec32(Dec32& d, const void* mlp, int lane) 
       d.c2[mc][r] = ld<MDT>(mlp, kOffB2 + 16 * mc + 4 * g + r);
     }
   }
-  float w3[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) w3[e] = ld<MDT>(mlp, kOffW3 + min(i & 3, 2) * 32 + unit_of(g, e));
+  for (int c = 0; c < 3; ++c)
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) d.a3[q][e] = ((i >> 2) == q && (i & 3) < 3) ? w3[e] : 0.0f;
+    for (int e = 0; e < 8; ++e) d.w3[c][e] = ld<MDT>(mlp, kOffW3 + c * 32 + unit_of(g, e));
 #pragma unroll
   for (int r = 0; r < 4; ++r) d.c3[r] = r < 3 ? ld<MDT>(mlp, kOffB3 + r) : 0.0f;
 }
 
-__device__ __forceinline__ void dec32_group(const Dec32& d, const float f[4], int q, f4v& acc) {
+__device__ __forceinline__ void dec32_group(const Dec32& d, const float f[4], float z[3]) {
   f4v p0 = d.c1[0], p1 = d.c1[1];
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
@@ -645,30 +584,72 @@ __device__ __forceinline__ void dec32_group(const Dec32& d, const float f[4], in
     h2[4 + r] = fmaxf(r1[r], 0.0f);
   }
 #pragma unroll
-  for (int m = 0; m < 8; ++m) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(d.a3[q][m], h2[m], acc, 0, 0, 0);
+  for (int c = 0; c < 3; ++c) {
+    float v = d.w3[c][0] * h2[0];
+#pragma unroll
+    for (int m = 1; m < 8; ++m) v = fmaf(d.w3[c][m], h2[m], v);
+    z[c] = v;
+  }
 }
 
-// Generic wrappers selected by precision.
+// Decoders by precision.  group(f, q, acc) takes 16 texels' inputs (lane (g, j): input_of(g,
+// 0..3) of texel 16q + j); after the four groups finish(acc) is the output layer of this
+// lane's own texel.
 template <int PREC> struct Dec;
 template <> struct Dec<NDGI_PREC_F16> {
   Dec16 d;
+  typedef f4v Acc;
   __device__ __forceinline__ void load(const void* mlp, int dt, int lane) {
     if (dt == NDGI_DTYPE_F16) load_dec16<NDGI_DTYPE_F16, false>(d, mlp, lane);
     else load_dec16<NDGI_DTYPE_F32, false>(d, mlp, lane);
   }
-  __device__ __forceinline__ void group(const float f[4], int q, f4v& acc) const {
+  // weights for texel centres (see load_dec16), used with texel_group
+  __device__ __forceinline__ void load_texel(const void* mlp, int dt, int lane) {
+    if (dt == NDGI_DTYPE_F16) load_dec16<NDGI_DTYPE_F16, true>(d, mlp, lane);
+    else load_dec16<NDGI_DTYPE_F32, true>(d, mlp, lane);
+  }
+  __device__ __forceinline__ Acc start() const { return d.c3; }
+  __device__ __forceinline__ void group(const float f[4], int q, Acc& acc) const {
     dec16_group(d, split_inputs(f), q, acc);
   }
-  __device__ __forceinline__ f4v bias3() const { return d.c3; }
+  __device__ __forceinline__ void texel_group(uint32_t sa, uint32_t sb, float ga, float gb, int q, Acc& acc) const {
+    dec16_group(d, texel_x(sa | (sb << 16) | 0x64006400u, ga, gb), q, acc);
+  }
+  __device__ __forceinline__ f4v finish(const Acc& acc) const { return acc; }
 };
 template <> struct Dec<NDGI_PREC_F32> {
   Dec32 d;
+  struct Acc {
+    float z[4][3];
+  };
   __device__ __forceinline__ void load(const void* mlp, int dt, int lane) {
     if (dt == NDGI_DTYPE_F16) load_dec32<NDGI_DTYPE_F16>(d, mlp, lane);
     else load_dec32<NDGI_DTYPE_F32>(d, mlp, lane);
   }
-  __device__ __forceinline__ void group(const float f[4], int q, f4v& acc) const { dec32_group(d, f, q, acc); }
-  __device__ __forceinline__ f4v bias3() const { return d.c3; }
+  __device__ __forceinline__ void load_texel(const void* mlp, int dt, int lane) { load(mlp, dt, lane); }
+  __device__ __forceinline__ Acc start() const { return Acc(); }
+  __device__ __forceinline__ void group(const float f[4], int q, Acc& acc) const { dec32_group(d, f, acc.z[q]); }
+  __device__ __forceinline__ void texel_group(uint32_t sa, uint32_t sb, float ga, float gb, int q, Acc& acc) const {
+    const float f[4] = {(float)sa * (1.0f / 255.0f), (float)sb * (1.0f / 255.0f), ga, gb};
+    dec32_group(d, f, acc.z[q]);
+  }
+  // The four lane groups' partial sums: an exchange of halves leaves groups 0 and 1 with
+  // texel groups 0, 1 and groups 2 and 3 with 2, 3 (two partials added), an exchange of
+  // neighbours then leaves lane group q with texel group q.
+  __device__ __forceinline__ f4v finish(const Acc& acc) const {
+    f4v o = d.c3;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      float a = acc.z[0][c], b = acc.z[2][c], e = acc.z[1][c], f = acc.z[3][c];
+      swap32(a, b);
+      swap32(e, f);
+      a += b;
+      e += f;
+      swap16(a, e);
+      o[c] += a + e;
+    }
+    return o;
+  }
 };
 
 // Phase B from registers: the decoder over the wave's 64 queries after the handoff; lane l
@@ -677,26 +658,10 @@ template <int PREC>
 __device__ __forceinline__ f4v decode_regs(const Dec<PREC>& dec, const float sp[8], const float gr[8]) {
   float r[4][4];
   transpose_chunks(sp, gr, r);
-  f4v acc = dec.bias3();
+  typename Dec<PREC>::Acc acc = dec.start();
 #pragma unroll
   for (int q = 0; q < 4; ++q) dec.group(r[q], q, acc);
-  return acc;
-}
-
-// Phase B: the decoder over the 64 queries of a wave's feature block; lane l ends with
-// the output-layer values of query l.
-template <int PREC>
-__device__ __forceinline__ f4v decode_feats(const Dec<PREC>& dec, const float* feat, int g, int j) {
-  f4v acc = dec.bias3();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float* r = feat + (16 * q + j) * kFeatStride;
-    const float2 sp = *(const float2*)(r + 2 * g);
-    const float2 gr = *(const float2*)(r + 8 + 2 * g);
-    const float f[4] = {sp.x, sp.y, gr.x, gr.y};
-    dec.group(f, q, acc);
-  }
-  return acc;
+  return dec.finish(acc);
 }
 
 // Store the RGB of one texel: exp of the output layer, FP16 (rounded once) or FP32.

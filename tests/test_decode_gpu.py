@@ -347,6 +347,40 @@ def _run_pages(N, ctx, models, reqs, prec, graph=False, n_serve=None, dst=None):
     torch.cuda.synchronize()
     return dst.float().cpu().numpy(), (dms, marr, rq, nreq)
 
+@pytest.mark.parametrize("prec,tol", [(1, TOL16), (0, TOL32)])
+@pytest.mark.parametrize("grid,page,shape", [
+    ((64, 64), 256, (2, 32)),      # a quarter of the texels: rows at fixed places, long slabs
+    ((64, 48), 48, (1, 3)),        # an odd number of passes a slab (a pass pair's second half missing)
+    ((32, 24), 256, (1, 32)),  # an eighth: several texel rows a grid row, row axes reloaded
+    ((1, 1), 64, (1, 1)),          # a single node
+    ((5, 192), 64, (2, 4)),        # one grid row a texel row
+    ((300, 401), 64, (4, 2)),      # finer than the texels: rows skipped
+])
+def test_page_rows_at_every_grid_ratio(N, prec, tol, grid, page, shape):
+    """Pages of a 256 x 192 map (padded to whole pages) over grids coarser and finer than the
+    texels, FP16 and FP32 storage, at sub-tile heights around the decoder's pass pairs."""
+    import torch
+    c = N.Context(0)
+    c.set_launch(shape[0], shape[1], 32)
+    W, H = 256, 256 if page == 256 else 192
+    models = [I.random_model(W, H, grid[0], grid[1], 5, gd, np.float16, config=64, index=i)
+              for i, gd in enumerate([np.float16, np.float32])]
+    reqs, off = [], 0
+    for i in range(2):
+        for px, py, t in ((0, 0, 0.13), (W // page - 1, H // page - 1, 0.97)):
+            reqs.append((i, px, py, np.float32(t), off))
+            off += page * page
+    dms = [N.DeviceModel.from_numpy(m) for m in models]
+    a = [np.array(v) for v in zip(*reqs)]
+    dst = torch.zeros((off, 3), dtype=torch.float16 if prec else torch.float32, device="cuda")
+    nreq = torch.tensor([len(reqs)], dtype=torch.int32, device="cuda")
+    c.decode_pages(N.models_array(dms), 2, N.page_requests(*a), nreq, len(reqs), page, dst, page, prec)
+    ref = np.zeros((off, 3))
+    assert O.decode_pages(models, reqs, page, ref, page) == 0
+    assert_rel(dst.float().cpu().numpy(), ref, tol, f"grid {grid} page {page} prec {prec}")
+    c.close()
+
+
 
 @pytest.mark.parametrize("prec,tol", [(1, TOL16), (0, TOL32)])
 def test_pages_many_models_and_bad_requests(N, ctx, prec, tol):
