@@ -8,16 +8,38 @@
 
 namespace ndgi {
 
+// How a map's texels read its parameters.  Fixed per kernel instance: a choice made at run
+// time around each texel's loads keeps them from being in flight together.
+enum { kSimBc4 = 0, kSimBc4Rounded = 1, kSimDirect = 2, kSimBc7 = 3, kSimBc7Rounded = 4 };
+template <int SIM> constexpr bool sim_bc7() { return SIM >= kSimBc7; }
+
+// The parameters of one texel: its footprint's endpoints [4][2] and its 4 weights (BC4 layout)
+// or its one weight (BC7).
+template <int SIM>
+struct TexRaw {
+  float4 ea, eb;
+  float4 w;   // BC7: w.x
+};
+template <int SIM>
+__device__ __forceinline__ TexRaw<SIM> tex_load(const float* __restrict__ ep, const float* __restrict__ w) {
+  TexRaw<SIM> r;
+  if constexpr (SIM != kSimDirect) {
+    r.ea = *(const float4*)ep;
+    r.eb = *(const float4*)(ep + 4);
+  }
+  if constexpr (sim_bc7<SIM>()) r.w.x = *w;
+  else r.w = *(const float4*)w;
+  return r;
+}
+
 // One 4-channel texel of a block-parameterised map: ep = the footprint's [4][2] endpoints,
 // w = the texel's 4 weights.  Rounded (bcsim): E = rint(fl32(255 e)), J = rint(fl32(7 w)),
 // value floor(((7-J) E1 + J E2 + 3) / 7) / 255 and the straight-through derivatives of
 // Eq. 7 at (E/255, J/7); otherwise Eq. 7 itself.
 struct BcTex { float v[4], d1[4], d2[4], dw[4]; };
-__device__ __forceinline__ BcTex bc_texel(const float* __restrict__ ep, const float* __restrict__ w, bool bcsim) {
+__device__ __forceinline__ BcTex bc_texel(const float4& ea, const float4& eb, const float4& wv, bool bcsim) {
 #pragma clang fp contract(off)
   BcTex r;
-  const float4 ea = *(const float4*)ep, eb = *(const float4*)(ep + 4);
-  const float4 wv = *(const float4*)w;
   const float e1[4] = {ea.x, ea.z, eb.x, eb.z}, e2[4] = {ea.y, ea.w, eb.y, eb.w}, ww[4] = {wv.x, wv.y, wv.z, wv.w};
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
@@ -63,10 +85,9 @@ __device__ __forceinline__ void bc7_endpoint(const float e[4], int E[4]) {
   for (int c = 0; c < 4; ++c) E[c] = p ? Ep[1][c] : Ep[0][c];
 }
 
-__device__ __forceinline__ BcTex bc7_texel(const float* __restrict__ ep, float w, bool bcsim) {
+__device__ __forceinline__ BcTex bc7_texel(const float4& ea, const float4& eb, float w, bool bcsim) {
 #pragma clang fp contract(off)
   BcTex r;
-  const float4 ea = *(const float4*)ep, eb = *(const float4*)(ep + 4);
   const float e1[4] = {ea.x, ea.z, eb.x, eb.z}, e2[4] = {ea.y, ea.w, eb.y, eb.w};
   if (bcsim) {
     int E1[4], E2[4];
@@ -93,14 +114,13 @@ __device__ __forceinline__ BcTex bc7_texel(const float* __restrict__ ep, float w
   return r;
 }
 
-// Texel of either codec: weights at w (4 per texel for BC4, 1 for BC7).  direct: the map is
-// its texel values themselves (4 per texel, the BC4 layout), endpoints unused.
-__device__ __forceinline__ BcTex sim_texel(const float* __restrict__ ep, const float* __restrict__ w, bool bcsim,
-                                           bool direct, int codec) {
-  if (direct) {
+// Texel from its loaded parameters.  kSimDirect: the map is its texel values themselves (4 per
+// texel, the BC4 layout), endpoints unused.
+template <int SIM>
+__device__ __forceinline__ BcTex sim_texel(const TexRaw<SIM>& p) {
+  if constexpr (SIM == kSimDirect) {
     BcTex r;
-    const float4 wv = *(const float4*)w;
-    const float ww[4] = {wv.x, wv.y, wv.z, wv.w};
+    const float ww[4] = {p.w.x, p.w.y, p.w.z, p.w.w};
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       r.v[c] = ww[c];
@@ -109,8 +129,11 @@ __device__ __forceinline__ BcTex sim_texel(const float* __restrict__ ep, const f
       r.dw[c] = 1.0f;
     }
     return r;
+  } else if constexpr (sim_bc7<SIM>()) {
+    return bc7_texel(p.ea, p.eb, p.w.x, SIM == kSimBc7Rounded);
+  } else {
+    return bc_texel(p.ea, p.eb, p.w, SIM == kSimBc4Rounded);
   }
-  return codec ? bc7_texel(ep, *w, bcsim) : bc_texel(ep, w, bcsim);
 }
 
 // Export reconstruction (Sec. 3.4, last paragraph of Feature Map Compression): the 8-bit

@@ -343,6 +343,16 @@ __device__ __forceinline__ void swap16(float& a, float& b) {
   a = __uint_as_float(p[0]);
   b = __uint_as_float(p[1]);
 }
+// Sum over the four lane groups of each group's partial zq (of texel group q), group q's sum
+// into lane group q: an exchange of halves leaves lane groups 0 and 1 with texel groups 0, 1 and
+// 2 and 3 with 2, 3 (two partials added), an exchange of neighbours the rest.
+__device__ __forceinline__ float sum_groups(float z0, float z1, float z2, float z3) {
+  swap32(z0, z2);
+  swap32(z1, z3);
+  float a = z0 + z2, b = z1 + z3;
+  swap16(a, b);
+  return a + b;
+}
 // The transpose itself: r[c] of lane (row g, j) goes to r[g] of lane (row c, j).
 __device__ __forceinline__ void transpose_rows(float r[4][4]) {
 #pragma unroll
@@ -633,21 +643,10 @@ template <> struct Dec<NDGI_PREC_F32> {
     const float f[4] = {(float)sa * (1.0f / 255.0f), (float)sb * (1.0f / 255.0f), ga, gb};
     dec32_group(d, f, acc.z[q]);
   }
-  // The four lane groups' partial sums: an exchange of halves leaves groups 0 and 1 with
-  // texel groups 0, 1 and groups 2 and 3 with 2, 3 (two partials added), an exchange of
-  // neighbours then leaves lane group q with texel group q.
   __device__ __forceinline__ f4v finish(const Acc& acc) const {
     f4v o = d.c3;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      float a = acc.z[0][c], b = acc.z[2][c], e = acc.z[1][c], f = acc.z[3][c];
-      swap32(a, b);
-      swap32(e, f);
-      a += b;
-      e += f;
-      swap16(a, e);
-      o[c] += a + e;
-    }
+    for (int c = 0; c < 3; ++c) o[c] += sum_groups(acc.z[0][c], acc.z[1][c], acc.z[2][c], acc.z[3][c]);
     return o;
   }
 };

@@ -10,10 +10,12 @@
 // centre and frame time fix every interpolation weight.  One launch trains any number of
 // models of the same sizes (the paper trains one model per virtual-texture tile): each
 // model owns a contiguous run of the batch, so every workgroup's samples share one model and
-// its decoder in LDS.  The decoder's forward runs in FP32 on the VALU from weights staged in
-// LDS (hidden 16 or 64); its weight gradients and its input gradients run on FP32 MFMA over
-// the wave's 64 samples (operands staged in LDS slabs); feature gradients go out as float
-// atomics, the contended F_uvt endpoint and plane ones summed in LDS per chunk first.
+// its decoder in LDS.  The decoder (hidden 16 or 64) runs on FP32 MFMA from weights staged in
+// LDS, forward, backward and its weight gradients (sums over the wave's 64 samples, operands
+// staged in LDS slabs); feature gradients go out as float atomics, F_uvt's and the planes'
+// summed in LDS per chunk first where they fit.
+#include <type_traits>
+
 #include "bcsim.hpp"
 #include "hybrid.hpp"
 #include "internal.hpp"
@@ -29,6 +31,7 @@ struct HybTrainDims {
   int W, H, Gu, Gv, S, U, V, Tt, hidden, frames;
   int M, Bm;                                          // models, samples per model
   int codec, cw;                                      // block format; weights per texel (4 or 1)
+  float inv2w, inv2h;                                 // 1 / (2 W), 1 / (2 H)
   int64_t o_uvw, o_tep, o_tw, o_ut, o_vt, o_mlp, n;   // segment offsets, parameters per model
 };
 
@@ -48,6 +51,8 @@ static HybTrainDims htd_of(const ndgi_hybrid_train_state* st) {
   d.Bm = st->per_model;
   d.codec = st->codec;
   d.cw = d.codec == NDGI_CODEC_BC7 ? 1 : 4;
+  d.inv2w = 1.0f / (float)(2 * d.W);
+  d.inv2h = 1.0f / (float)(2 * d.H);
   d.o_uvw = (int64_t)(d.H / 4) * (d.W / 4) * 4 * 2;
   d.o_tep = d.o_uvw + (int64_t)d.H * d.W * d.cw;
   d.o_tw = d.o_tep + (int64_t)d.S * (d.Gv / 4) * (d.Gu / 4) * 4 * 2;
@@ -83,25 +88,52 @@ __device__ __forceinline__ double wave_sum_d(double v) {
 // A workgroup of 1, 2 or 4 waves takes chunks of consecutive samples of one model.  When
 // the model's F_uvt endpoints and F_ut / F_vt planes fit in LDS (kAccMaxBytes), their
 // gradients, the most contended ones (a footprint's endpoints collect every sample that
-// taps it), are summed in LDS over the chunk and added to HBM once per chunk.
+// taps it), are summed in LDS over the chunk and added to HBM once per chunk; so are F_uvt's
+// weights (one a texel, BC7) where they fit beside them.  8 waves a workgroup are slower (163
+// against 152 us, 64 M-profile models x 4096 samples: half as many chunks share an
+// accumulator's zeroing and flush, but the adds of 8 waves meet in it).
 constexpr int kHtMaxThreads = 256;
 constexpr int64_t kAccMaxBytes = 64 * 1024;
 
-// The slabs are private to their wave: ordering a wave's writes before its lanes' reads is a
-// wavefront-scope fence (wave_sync), and the waves of a workgroup never wait for each other
-// inside a round.
-// Decoder weight and bias gradients are sums over the wave's 64 samples of outer products
-// of per-sample vectors, computed on MFMA with the samples as K: each operand is staged in
-// an LDS slab [64 samples][16 units] (sample-major, written by the sample's lane).  Lane
-// (g, i) = (lane >> 4, lane & 15) supplies sample 4 q + g, unit i of both slabs at K step q;
-// the 16 x 16 result sits in lane (g, i), element r, as row 4 g + r, column i.
-constexpr int kSlab = 64 * 16;
-constexpr int kSlabsPerWave = 3;   // A, B, and C holding the decoder inputs during the backward
+// The decoder runs on FP32 MFMA (v_mfma_f32_16x16x4_f32) forward and backward, in the layout of
+// the decode kernels: the wave's 64 samples are 4 groups of 16, and of group q lane (g, j) =
+// (lane >> 4, lane & 15) holds 4 units of a 16-unit block of sample 16q + j, which are both a
+// layer's result and its K share of the next product.  They are units 4r + g (r = 0..3), not
+// 4g + r: MFMA r of a product then adds K = 4r .. 4r + 3, so a sum runs from the bias through
+// the inputs in order, one FMA each, as a plain loop does, and a prediction has the bits of that
+// loop (the loss, a mean in FP64, does not move with the kernel's layout).  The decoder is
+// staged with its units in that order, so that a lane's four are consecutive in LDS.  Features
+// and their gradients are per sample (lane l = sample l); a register transpose
+// (transpose_rows) goes from one to the other.
+//
+// Place 4g + r of a 16-unit block holds unit 4r + g, and the reverse.
+__device__ __forceinline__ int unit_at(int p) { return (p & ~15) | ((p & 3) << 2) | ((p >> 2) & 3); }
+// Where weight i of the decoder is staged.
+template <int HD>
+__device__ __forceinline__ int staged(int i) {
+  using Sh = HybShape<HD>;
+  if (i < Sh::oB1) return unit_at((i - Sh::oW1) / 16) * 16 + unit_at((i - Sh::oW1) % 16) + Sh::oW1;
+  if (i < Sh::oW2) return Sh::oB1 + unit_at(i - Sh::oB1);
+  if (i < Sh::oB2) return Sh::oW2 + unit_at((i - Sh::oW2) / HD) * HD + unit_at((i - Sh::oW2) % HD);
+  if (i < Sh::oW3) return Sh::oB2 + unit_at(i - Sh::oB2);
+  if (i < Sh::oB3) return Sh::oW3 + (i - Sh::oW3) / HD * HD + unit_at((i - Sh::oW3) % HD);
+  return i;
+}
 
-__device__ __forceinline__ void slab_store(float* slab, int lane, const float v[16]) {
-  f4v* d = (f4v*)(slab + lane * 16);   // one vector type for every slab access
+// Decoder weight gradients are sums over the wave's 64 samples of outer products of per-sample
+// vectors, on MFMA with the samples as K: each operand is staged in an LDS slab [64 samples][16
+// units].  Lane (g, i) supplies sample 4 q + g, unit i of both slabs at K step q; the 16 x 16
+// result sits in lane (g, i), element r, as row 4 g + r, column i.  The slabs are private to
+// their wave: ordering a wave's writes before its lanes' reads is a wavefront-scope fence
+// (wave_sync), and the waves of a workgroup never wait for each other inside a round.
+constexpr int kSlab = 64 * 16;
+constexpr int kWaveLds = 2 * kSlab + 512;   // floats a wave: two slabs, and offsets of the scatter staging
+
+// A block's values of the 4 groups into a slab.
+__device__ __forceinline__ void slab_store(float* slab, int lane, const f4v v[4]) {
+  const int g = lane >> 4, j = lane & 15;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) d[q] = f4v{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+  for (int q = 0; q < 4; ++q) *(f4v*)(slab + (16 * q + j) * 16 + 4 * g) = v[q];
 }
 
 // D[u][c] = acc + sum over samples of A[s][u] B[s][c]
@@ -122,6 +154,33 @@ __device__ __forceinline__ f4v slab_sum(const float* A, int lane, f4v acc = f4v{
   return acc;
 }
 
+// The same with A's rows 0..2 only (its other columns are not written).
+__device__ __forceinline__ f4v slab_outer_rows(const float* A, const float* B, int lane, f4v acc) {
+  const int g = lane >> 4, i = lane & 15;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const float a = A[(4 * q + g) * 16 + min(i, 3)];   // column 3 holds the zero channel
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, B[(4 * q + g) * 16 + i], acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+// acc + W x for one group: W's K share of this lane in w, the group's in x
+__device__ __forceinline__ f4v mfma16(const f4v& w, const f4v& x, f4v acc) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[m], x[m], acc, 0, 0, 0);
+  return acc;
+}
+
+// slab_sum of the same rows
+__device__ __forceinline__ f4v slab_sum_rows(const float* A, int lane, f4v acc) {
+  const int g = lane >> 4, i = lane & 15;
+#pragma unroll
+  for (int q = 0; q < 16; ++q)
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(A[(4 * q + g) * 16 + min(i, 3)], 1.0f, acc, 0, 0, 0);
+  return acc;
+}
+
 // Float adds into a model's gradients in global memory, staged by the wave: lane s wrote R
 // runs of L consecutive words, run r at sv[(s R + r) L ..] to words so[s R + r] + 0..L-1 of
 // G (a negative offset skips the run).  An atomic add costs one memory request per 64-byte
@@ -132,7 +191,7 @@ __device__ __forceinline__ f4v slab_sum(const float* A, int lane, f4v acc = f4v{
 template <int R, int L>
 __device__ __forceinline__ void ht_scatter(float* G, const float* sv, const int* so, int lane) {
   wave_sync();   // the staging is visible to the wave
-#pragma unroll 1
+#pragma unroll 4
   for (int t = 0; t < R * L; ++t) {
     const int e = 64 * t + lane;
     const int o = so[e / L];
@@ -142,39 +201,75 @@ __device__ __forceinline__ void ht_scatter(float* G, const float* sv, const int*
   wave_sync();   // the slabs may be staged again
 }
 
+// texel_axis<false>(x, G, S) with inv = 1 / (2 S) rounded to nearest, and no division.  The
+// numerator is below 2^25 (W, H and the grids stay within 4096), so the rounded quotient is off
+// by one at most and the remainder says which way; the weight r / (2 S) is the product with
+// inv and one Newton correction by the exact residual, which rounds as the division does
+// (Markstein 1990: correct for a correctly rounded reciprocal).
+__device__ __forceinline__ Axis sample_axis(int x, int G, int S, float inv) {
+  const int num = (2 * x + 1) * G - S, den = 2 * S;
+  int q = (int)floorf((float)num * inv);
+  int r = num - q * den;
+  q = r < 0 ? q - 1 : (r >= den ? q + 1 : q);
+  r = r < 0 ? r + den : (r >= den ? r - den : r);
+  Axis a;
+  a.i0 = min(max(q, 0), G - 1);
+  a.i1 = min(max(q + 1, 0), G - 1);
+  const float n = (float)r, d = (float)den, w = n * inv;
+  a.w1 = fmaf(fmaf(-w, d, n), inv, w);
+  a.w0 = 1.0f - a.w1;
+  return a;
+}
+
 // Where a training sample reads its features: the F_uvt taps (bilinear in the grid, linear
-// between slices), the F_ut / F_vt taps, and F_uv's footprint.
+// between slices), the F_ut / F_vt taps, and F_uv's footprint.  Word offsets into the model's
+// block are 32-bit (the host bounds it).
 struct SampleTaps {
   Axis gx, gy, pu, pv;
   NodeT ns, nk;
   float tw[4];
-  int txs[4], tys[4];
-  int64_t fpu;
+  int fp[2][4], wi[2][4];   // per slice and tap: footprint, and word offset of its weights in F_uvt's
+  int fpu, wu;              // F_uv: footprint, word offset of the weights in F_uv's
 };
 __device__ __forceinline__ SampleTaps sample_taps(const HybTrainDims& d, int x, int y, float tau) {
   SampleTaps T;
-  T.gx = texel_axis<false>(x, d.Gu, d.W);
-  T.gy = texel_axis<false>(y, d.Gv, d.H);
+  T.gx = sample_axis(x, d.Gu, d.W, d.inv2w);
+  T.gy = sample_axis(y, d.Gv, d.H, d.inv2h);
   T.ns = node_axis(tau, d.S);
   T.nk = node_axis(tau, d.Tt);
   tap_weights(T.gx, T.gy, T.tw);
-  const int txs[4] = {T.gx.i0, T.gx.i1, T.gx.i0, T.gx.i1}, tys[4] = {T.gy.i0, T.gy.i0, T.gy.i1, T.gy.i1};
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    T.txs[i] = txs[i];
-    T.tys[i] = tys[i];
-  }
-  T.fpu = (int64_t)(y >> 2) * (d.W / 4) + (x >> 2);
-  T.pu = texel_axis<false>(x, d.U, d.W);
-  T.pv = texel_axis<false>(y, d.V, d.H);
+  for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int si = sl ? T.ns.i1 : T.ns.i0, tx = (i & 1) ? T.gx.i1 : T.gx.i0, ty = (i & 2) ? T.gy.i1 : T.gy.i0;
+      T.fp[sl][i] = (si * (d.Gv >> 2) + (ty >> 2)) * (d.Gu >> 2) + (tx >> 2);
+      T.wi[sl][i] = ((si * d.Gv + ty) * d.Gu + tx) * d.cw;
+    }
+  T.fpu = (y >> 2) * (d.W >> 2) + (x >> 2);
+  T.wu = (y * d.W + x) * d.cw;
+  T.pu = sample_axis(x, d.U, d.W, d.inv2w);
+  T.pv = sample_axis(y, d.V, d.H, d.inv2h);
   return T;
 }
 
 // MODE: NDGI_TRAIN_FORWARD writes pred; NDGI_TRAIN_LOSS_GRAD adds the loss and gradients.
 // Dynamic LDS: per wave the MFMA operand slabs A, B ([64][16] each), then, with `accum`,
-// the accumulators [F_uvt endpoints (nE) | F_ut, F_vt (nP)] of the chunk's model.
+// the accumulators [F_uvt endpoints | F_ut, F_vt | F_uvt weights (accum = 2)] of the chunk's model.
 // `chunk` is a multiple of blockDim.x and, with several models, divides the per-model count.
-template <int HD, int MODE>
+// SIM: how the maps' texels read the parameters (one of the kSim kinds, the state's layout with it).
+//
+// What bounds it: one wave a SIMD (the backward's registers and the accumulators' LDS), so a
+// round is the sum of its latencies and of what it issues.  64 M-profile models x 4096 samples,
+// BC7 layout, noise, one step: 185 us with the decoder forward on the VALU, the texels' kind
+// chosen at run time and each tap's parameters loaded when used; 174 with SIM fixed per instance,
+// all gathers of a sample in flight together, 32-bit offsets, axes without divisions and
+// conflict-free accumulators; 162 with a model's chunks on one XCD; 160 with the decoder on
+// MFMA; 152 with F_uvt's weights summed in LDS.  Of the 152, the adds into HBM are about 30, the
+// LDS adds 8, and 27 are not the rounds (Adam 16, launches, prologue, flush).  Per-lane bias sums
+// reduced at a chunk's end were 3 us faster than slab_sum, but add in another order.  h = 64 (16
+// models): 152 before, 126 now.
+template <int HD, int MODE, int SIM>
 __global__ __launch_bounds__(kHtMaxThreads) void k_hybrid_train(HybTrainDims d, const float* __restrict__ Pall,
                                                                  float* __restrict__ Gall,
                                                                  const float* __restrict__ keys,
@@ -185,21 +280,33 @@ __global__ __launch_bounds__(kHtMaxThreads) void k_hybrid_train(HybTrainDims d, 
                                                                  double* __restrict__ loss_acc, int64_t chunk,
                                                                  int accum) {
   using Sh = HybShape<HD>;
-  __shared__ float sw[Sh::kSize];
+  constexpr int NB = HD / 16;
+  __shared__ __align__(16) float sw[(Sh::kSize + 3) / 4 * 4];
   extern __shared__ __align__(16) float dyn[];   // 16-byte aligned: float4 slab accesses
   const int nthr = blockDim.x, waves = nthr >> 6;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lg = lane >> 4, li = lane & 15;
-  float* const slA = dyn + wave * kSlabsPerWave * kSlab;
+  const int ui = unit_at(li);
+  float* const slA = dyn + wave * kWaveLds;
   float* const slB = slA + kSlab;
-  float* const slC = slB + kSlab;
-  float* const acc = dyn + waves * kSlabsPerWave * kSlab;
-  const int64_t nE = (int64_t)d.S * (d.Gv / 4) * (d.Gu / 4) * 8, nP = d.o_mlp - d.o_ut;
-  const bool bcsim = flags & NDGI_HTRAIN_BCSIM, noise = flags & NDGI_HTRAIN_NOISE, qplanes = flags & NDGI_HTRAIN_QPLANES;
-  const bool direct = flags & NDGI_HTRAIN_DIRECT;
+  float* const acc = dyn + waves * kWaveLds;
+  // LDS accumulators: F_uvt endpoints as [8 words of a footprint][footprints + 8] and the planes
+  // as [2 channels][texels], so that the adds of a wave, one word of 64 footprints or texels, fall
+  // on as many banks as they can
+  const int nF = d.S * (d.Gv / 4) * (d.Gu / 4), sF = nF + 8;
+  const int nT = (int)((d.o_mlp - d.o_ut) / 2), oP = 8 * sF;
+  // and, where they fit too (accum = 2), F_uvt's weights in their own order
+  const int oW = oP + 2 * nT, nW = accum > 1 ? (int)(d.o_ut - d.o_tw) : 0;
+  const bool noise = flags & NDGI_HTRAIN_NOISE, qplanes = flags & NDGI_HTRAIN_QPLANES;
+  constexpr bool direct = SIM == kSimDirect;
+  constexpr bool bc7 = sim_bc7<SIM>();
   const int64_t nchunks = (n + chunk - 1) / chunk;
   const int rounds = (int)(chunk / nthr);
   int cur = -1;
-  for (int64_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
+  // Workgroups go to the 8 XCDs round-robin: consecutive chunks, which are mostly of one model, are
+  // given to workgroups of one XCD, so that a model's parameters and the atomics into its
+  // gradients stay in one L2.
+  const int first = (gridDim.x & 7) == 0 ? (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) : (int)blockIdx.x;
+  for (int64_t ch = first; ch < nchunks; ch += gridDim.x) {
     const int64_t c0 = ch * chunk;
     const int m = (int)min(c0 / d.Bm, (int64_t)d.M - 1);   // the chunk lies inside one model's samples
     const float* P = Pall + (int64_t)m * d.o_mlp;
@@ -211,17 +318,18 @@ __global__ __launch_bounds__(kHtMaxThreads) void k_hybrid_train(HybTrainDims d, 
     // chunk; h = 64 adds each round's (its sums would hold 85 more registers a lane)
     constexpr bool kChain = HD == 16;
     f4v cw3 = {0.0f, 0.0f, 0.0f, 0.0f}, cb3 = cw3, cw2 = cw3, cb2 = cw3, cw1 = cw3, cb1 = cw3;
+    double loss = 0.0;   // this lane's samples of the chunk
   for (int r = 0; r < rounds; ++r) {
     // staging inside the round loop (first round only): the decoder weight reads of the
     // round cannot then be hoisted out of the loop into registers held across all rounds
     if (r == 0) {
       __syncthreads();   // the previous chunk's readers of sw and acc are done
       if (m != cur) {
-        for (int i = threadIdx.x; i < Sh::kSize; i += nthr) sw[i] = Pall[mlp_off + i];
+        for (int i = threadIdx.x; i < Sh::kSize; i += nthr) sw[staged<HD>(i)] = Pall[mlp_off + i];
         cur = m;
       }
       if (accum)
-        for (int64_t i = threadIdx.x; i < nE + nP; i += nthr) acc[i] = 0.0f;
+        for (int i = threadIdx.x; i < oW + nW; i += nthr) acc[i] = 0.0f;
       __syncthreads();
     }
     const int64_t s = c0 + (int64_t)r * nthr + threadIdx.x;
@@ -231,56 +339,58 @@ __global__ __launch_bounds__(kHtMaxThreads) void k_hybrid_train(HybTrainDims d, 
     const int f = min((int)(word >> 24), d.frames - 1);
     const float tau = d.frames > 1 ? (float)f / (float)(d.frames - 1) : 0.0f;
     const float t = keys ? keys[f] : tau;
-    // ---- features
+    // ---- features: every parameter the sample reads is loaded before any is used
     float xin[16];
-    auto plane_at = [&](int64_t off, int size, int k, int a, int c) {
-      const float v = P[off + ((int64_t)k * size + a) * 2 + c];
-      return qplanes ? rintf(__fmul_rn(255.0f, v)) * (1.0f / 255.0f) : v;
-    };
     {
-    const SampleTaps T = sample_taps(d, x, y, tau);
-    const NodeT &ns = T.ns, &nk = T.nk;
-    const float* tw = T.tw;
-    const int *txs = T.txs, *tys = T.tys;
-    const int64_t fpu = T.fpu;
+      const SampleTaps T = sample_taps(d, x, y, tau);
+      TexRaw<SIM> raw[2][4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) xin[c] = 0.0f;
+      for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
-    for (int sl = 0; sl < 2; ++sl) {
-      const int si = sl ? ns.i1 : ns.i0;
-      const float ws = sl ? ns.w1 : ns.w0;
+        for (int i = 0; i < 4; ++i) raw[sl][i] = tex_load<SIM>(P + d.o_tep + 8 * T.fp[sl][i], P + d.o_tw + T.wi[sl][i]);
+      const TexRaw<SIM> ru = tex_load<SIM>(P + 8 * T.fpu, P + d.o_uvw + T.wu);
+      float2 pv[2][2][2];   // plane, time row, position
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int64_t fp = ((int64_t)si * (d.Gv / 4) + (tys[i] >> 2)) * (d.Gu / 4) + (txs[i] >> 2);
-        const BcTex b = sim_texel(P + d.o_tep + fp * 8, P + d.o_tw + (((int64_t)si * d.Gv + tys[i]) * d.Gu + txs[i]) * d.cw,
-                                  bcsim, direct, d.codec);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) xin[c] = fmaf(ws * tw[i], b.v[c], xin[c]);
-      }
-    }
-    {
-      const BcTex bu = sim_texel(P + fpu * 8, P + d.o_uvw + ((int64_t)y * d.W + x) * d.cw, bcsim, direct, d.codec);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) xin[4 + c] = bu.v[c];
-    }
-    const Axis &pu = T.pu, &pv = T.pv;
-#pragma unroll
-    for (int pl = 0; pl < 2; ++pl) {
-      const int64_t off = pl ? d.o_vt : d.o_ut;
-      const int size = pl ? d.V : d.U;
-      const Axis& a = pl ? pv : pu;
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        float acc = 0.0f;
+      for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-          for (int aa = 0; aa < 2; ++aa)
-            acc = fmaf((kk ? nk.w1 : nk.w0) * (aa ? a.w1 : a.w0),
-                       plane_at(off, size, kk ? nk.i1 : nk.i0, aa ? a.i1 : a.i0, c), acc);
-        xin[8 + 2 * pl + c] = acc;
+          for (int aa = 0; aa < 2; ++aa) {
+            const Axis& a = pl ? T.pv : T.pu;
+            const int at = (kk ? T.nk.i1 : T.nk.i0) * (pl ? d.V : d.U) + (aa ? a.i1 : a.i0);
+            pv[pl][kk][aa] = *(const float2*)(P + (pl ? d.o_vt : d.o_ut) + 2 * at);
+          }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) xin[c] = 0.0f;
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl) {
+        const float ws = sl ? T.ns.w1 : T.ns.w0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const BcTex b = sim_texel<SIM>(raw[sl][i]);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) xin[c] = fmaf(ws * T.tw[i], b.v[c], xin[c]);
+        }
       }
-    }
+      const BcTex bu = sim_texel<SIM>(ru);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) xin[4 + c] = bu.v[c];
+      auto plane = [&](float v) { return qplanes ? rintf(__fmul_rn(255.0f, v)) * (1.0f / 255.0f) : v; };
+#pragma unroll
+      for (int pl = 0; pl < 2; ++pl) {
+        const Axis& a = pl ? T.pv : T.pu;
+        float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+          for (int aa = 0; aa < 2; ++aa) {
+            const float w = (kk ? T.nk.w1 : T.nk.w0) * (aa ? a.w1 : a.w0);
+            s0 = fmaf(w, plane(pv[pl][kk][aa].x), s0);
+            s1 = fmaf(w, plane(pv[pl][kk][aa].y), s1);
+          }
+        xin[8 + 2 * pl] = s0;
+        xin[9 + 2 * pl] = s1;
+      }
     }
     if (noise) {
 #pragma unroll
@@ -294,30 +404,71 @@ __global__ __launch_bounds__(kHtMaxThreads) void k_hybrid_train(HybTrainDims d, 
       xin[14] = 2.0f * sn * cs;
       xin[15] = fmaf(cs, cs, -sn * sn);
     }
-    // ---- decoder forward.  Only the layer-2 pre-activations are kept: a layer-1
-    // pre-activation is recomputed (the same FMA chain) wherever it is needed again, so the
-    // backward holds one 16-unit block of them at a time.
-    auto pre1 = [&](int j) {
-      float acc = sw[Sh::oB1 + j];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc = fmaf(sw[Sh::oW1 + j * 16 + i], xin[i], acc);
-      return acc;
+    // ---- decoder forward
+    // operands of the weights from LDS: rows of W (forward) and of its transpose (backward)
+    auto w_row = [&](int off, int row, int ld, int col) { return *(const f4v*)(sw + off + row * ld + col); };
+    auto w_col = [&](int off, int row, int ld, int col) {
+      return f4v{sw[off + row * ld + col], sw[off + (row + 1) * ld + col], sw[off + (row + 2) * ld + col],
+                 sw[off + (row + 3) * ld + col]};
     };
-    float a2[HD];
+    auto bias = [&](int off, int k) { return f4v{sw[off + 16 * k + 4 * lg], sw[off + 16 * k + 4 * lg + 1],
+                                                 sw[off + 16 * k + 4 * lg + 2], sw[off + 16 * k + 4 * lg + 3]}; };
+    auto gelu4 = [](const f4v& v) {
+      return f4v{gelu<NDGI_PREC_F32>(v[0]), gelu<NDGI_PREC_F32>(v[1]), gelu<NDGI_PREC_F32>(v[2]), gelu<NDGI_PREC_F32>(v[3])};
+    };
+    f4v xq[4];   // inputs 4g .. 4g + 3 of sample 16q + j
+    {
+      float t4[4][4];
 #pragma unroll
-    for (int j = 0; j < HD; ++j) a2[j] = sw[Sh::oB2 + j];
+      for (int c = 0; c < 16; ++c) t4[c & 3][c >> 2] = xin[c];
+      transpose_rows(t4);
 #pragma unroll
-    for (int k = 0; k < HD; ++k) {
-      const float h = gelu<NDGI_PREC_F32>(pre1(k));
-#pragma unroll
-      for (int j = 0; j < HD; ++j) a2[j] = fmaf(sw[Sh::oW2 + j * HD + k], h, a2[j]);
+      for (int q = 0; q < 4; ++q) xq[q] = f4v{t4[q][0], t4[q][1], t4[q][2], t4[q][3]};
     }
-    float out[3] = {sw[Sh::oB3], sw[Sh::oB3 + 1], sw[Sh::oB3 + 2]};
+    f4v a1[NB][4], a2[NB][4];
 #pragma unroll
-    for (int j = 0; j < HD; ++j) {
-      const float h = gelu<NDGI_PREC_F32>(a2[j]);
+    for (int k = 0; k < NB; ++k) {
+      const f4v w = w_row(Sh::oW1, 16 * k + li, 16, 4 * lg), b = bias(Sh::oB1, k);
 #pragma unroll
-      for (int c = 0; c < 3; ++c) out[c] = fmaf(sw[Sh::oW3 + c * HD + j], h, out[c]);
+      for (int q = 0; q < 4; ++q) a1[k][q] = mfma16(w, xq[q], b);
+    }
+#pragma unroll
+    for (int o = 0; o < NB; ++o) {
+      const f4v b = bias(Sh::oB2, o);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a2[o][q] = b;
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      f4v h[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) h[q] = gelu4(a1[k][q]);
+#pragma unroll
+      for (int o = 0; o < NB; ++o) {
+        const f4v w = w_row(Sh::oW2, 16 * o + li, HD, 16 * k + 4 * lg);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a2[o][q] = mfma16(w, h[q], a2[o][q]);
+      }
+    }
+    // output layer: rows 4g + c of the operand are all output c, so every lane group holds the
+    // outputs of every sample, and lane (g, j) takes group g's: lane l ends with sample l
+    float out[3];
+    {
+      f4v z[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) z[q] = f4v{sw[Sh::oB3], sw[Sh::oB3 + 1], sw[Sh::oB3 + 2], 0.0f};
+#pragma unroll
+      for (int k = 0; k < NB; ++k) {
+        f4v w = w_row(Sh::oW3, min(li & 3, 2), HD, 16 * k + 4 * lg);
+        if ((li & 3) == 3) w = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) z[q] = mfma16(w, gelu4(a2[k][q]), z[q]);
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const float lo = lg & 1 ? z[1][c] : z[0][c], hi = lg & 1 ? z[3][c] : z[2][c];
+        out[c] = lg & 2 ? hi : lo;
+      }
     }
     if constexpr (MODE == NDGI_TRAIN_FORWARD) {
       if (live) {
@@ -336,167 +487,142 @@ __global__ __launch_bounds__(kHtMaxThreads) void k_hybrid_train(HybTrainDims d, 
         sq += (double)e * (double)e;
         dout[c] = 2.0f * inv3n * e;
       }
-      sq = wave_sum_d(sq);
-      if (lane == 0) atomicAdd(loss_acc, sq * loss_w);
-      // ---- decoder backward.  Layer 3: dW3[c][j] = sum dout[c] h2[j], db3 = sum dout
+      loss += sq;
+      // ---- decoder backward.  Lane (g, j) of group q takes channel g of sample 16q + j.
+      float dq[4];
       {
-        float v[16];
+        float t4[4] = {dout[0], dout[1], dout[2], 0.0f};
+        swap32(t4[0], t4[2]);
+        swap32(t4[1], t4[3]);
+        swap16(t4[0], t4[1]);
+        swap16(t4[2], t4[3]);
 #pragma unroll
-        for (int c = 0; c < 16; ++c) v[c] = c < 3 ? dout[c] : 0.0f;
-        slab_store(slA, lane, v);
+        for (int q = 0; q < 4; ++q) dq[q] = t4[q];
       }
+      // h = 64: the activations are computed again from a1 and a2 rather than kept (128 registers)
+      if constexpr (!kChain) {
 #pragma unroll
-      for (int jb = 0; jb < HD / 16; ++jb) {
-        float v[16];
+        for (int k = 0; k < NB; ++k)
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = gelu<NDGI_PREC_F32>(a2[16 * jb + u]);
-        slab_store(slB, lane, v);
+          for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(a1[k][q]), "+v"(a2[k][q]));
+      }
+      // the round's own copy of the base: the addresses of its adds are not kept across rounds
+      float* gr = gm;
+      if constexpr (!kChain) asm volatile("" : "+v"(gr));
+      // Layer 3: dW3[c][j] = sum dout[c] h2[j]; then a2 becomes d loss / d a2
+#pragma unroll
+      for (int q = 0; q < 4; ++q) slA[(16 * q + li) * 16 + lg] = dq[q];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) {
+        if constexpr (NB > 1) __builtin_amdgcn_sched_barrier(0);
+        f4v h[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) h[q] = gelu4(a2[k][q]);
+        slab_store(slB, lane, h);
         wave_sync();
+        const f4v w3 = slab_outer_rows(slA, slB, lane, kChain ? cw3 : f4v{0.0f, 0.0f, 0.0f, 0.0f});
+        f4v b3;
+        if (k == 0) b3 = slab_sum_rows(slA, lane, kChain ? cb3 : f4v{0.0f, 0.0f, 0.0f, 0.0f});
         if constexpr (kChain) {
-          cw3 = slab_outer(slA, slB, lane, cw3);
-          cb3 = slab_sum(slA, lane, cb3);
+          cw3 = w3;
+          cb3 = b3;
         } else {
-          const f4v w3 = slab_outer(slA, slB, lane);
           if (lg == 0) {
 #pragma unroll
-            for (int r = 0; r < 3; ++r) atomicAdd(gm + Sh::oW3 + r * HD + 16 * jb + li, w3[r]);
+            for (int r = 0; r < 3; ++r) atomicAdd(gr + Sh::oW3 + r * HD + 16 * k + ui, w3[r]);
           }
-          if (jb == 0) {
-            const f4v b3 = slab_sum(slA, lane);
-            if (lane == 0) {
+          if (k == 0 && lane == 0) {
 #pragma unroll
-              for (int r = 0; r < 3; ++r) atomicAdd(gm + Sh::oB3 + r, b3[r]);
-            }
+            for (int r = 0; r < 3; ++r) atomicAdd(gr + Sh::oB3 + r, b3[r]);
           }
         }
         wave_sync();
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int j = 0; j < HD; ++j) {
-        float dh = 0.0f;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) dh = fmaf(sw[Sh::oW3 + c * HD + j], dout[c], dh);
-        a2[j] = dh * gelu_grad(a2[j]);   // a2 now holds d loss / d a2
-      }
-      // Layers 2 and 1, one 16-unit block kb of layer 1 at a time.  Layer 2: dW2[j][k] =
-      // sum g2[j] h1[k], db2 = sum g2 (g2 = d loss / d a2); the input gradient DH[k][s] =
-      // sum_j W2[j][k] g2[s][j] on MFMA as well (W2 from LDS as the A operand, the staged g2
-      // slab as B), handed back to the sample lanes through LDS, giving the block's
-      // g1 = DH gelu'(a1).  Layer 1 for that block: dW1[k][i] = sum g1[k] x[i], db1 = sum g1,
-      // and its share of the input gradient DX[i][s] = sum_k W1[k][i] g1[s][k], on MFMA.
-      slab_store(slC, lane, xin);
-      // the decoder inputs are read back from the lane's own row of slab C (written by this
-      // lane, so no barrier) rather than kept in registers through the backward
-      auto pre1c = [&](int j) {
-        const f4v* xr = (const f4v*)(slC + lane * 16);
-        float acc = sw[Sh::oB1 + j];
+        const float wt = lg < 3 ? sw[Sh::oW3 + min(lg, 2) * HD + 16 * k + li] : 0.0f;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const f4v xq = xr[q];
+          const f4v dh = __builtin_amdgcn_mfma_f32_16x16x4f32(wt, dq[q], f4v{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc = fmaf(sw[Sh::oW1 + j * 16 + 4 * q + e], xq[e], acc);
+          for (int r = 0; r < 4; ++r) a2[k][q][r] = dh[r] * gelu_grad<false>(a2[k][q][r]);
         }
-        return acc;
-      };
-      f4v dx4[4];
+      }
+      // Layers 2 and 1, one 16-unit block k of layer 1 at a time: dW2[j][k] = sum g2[j] h1[k]
+      // (g2 = d loss / d a2), the block's g1 = (W2^T g2) gelu'(a1), dW1[k][i] = sum g1[k] x[i] and
+      // its share of the input gradient W1^T g1.
+      f4v dxq[4];
 #pragma unroll
-      for (int sb = 0; sb < 4; ++sb) dx4[sb] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 1
-      for (int kb = 0; kb < HD / 16; ++kb) {
-        float a1b[16];
+      for (int q = 0; q < 4; ++q) dxq[q] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int u = 0; u < 16; ++u) a1b[u] = pre1c(16 * kb + u);
-        {
-          float v[16];
+      for (int k = 0; k < NB; ++k) {
+        if constexpr (NB > 1) __builtin_amdgcn_sched_barrier(0);
+        f4v t[4];
 #pragma unroll
-          for (int u = 0; u < 16; ++u) v[u] = gelu<NDGI_PREC_F32>(a1b[u]);
-          slab_store(slB, lane, v);
-        }
-        f4v dh4[4];
+        for (int q = 0; q < 4; ++q) t[q] = gelu4(a1[k][q]);
+        slab_store(slB, lane, t);
 #pragma unroll
-        for (int sb = 0; sb < 4; ++sb) dh4[sb] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int q = 0; q < 4; ++q) t[q] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int jb = 0; jb < HD / 16; ++jb) {
-          slab_store(slA, lane, a2 + 16 * jb);
+        for (int o = 0; o < NB; ++o) {
+          if constexpr (NB > 1) __builtin_amdgcn_sched_barrier(0);
+          slab_store(slA, lane, a2[o]);
           wave_sync();
           if constexpr (kChain) {
             cw2 = slab_outer(slA, slB, lane, cw2);
             cb2 = slab_sum(slA, lane, cb2);
           } else {
-            const f4v w2 = slab_outer(slA, slB, lane);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) atomicAdd(gm + Sh::oW2 + (16 * jb + 4 * lg + r) * HD + 16 * kb + li, w2[r]);
-            if (kb == 0) {
+            if (k == 0) {
               const f4v b2 = slab_sum(slA, lane);
               if (li == 0) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) atomicAdd(gm + Sh::oB2 + 16 * jb + 4 * lg + r, b2[r]);
+                for (int r = 0; r < 4; ++r) atomicAdd(gr + Sh::oB2 + 16 * o + 4 * r + lg, b2[r]);
               }
             }
-          }
+            const f4v w2 = slab_outer(slA, slB, lane);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float wa = sw[Sh::oW2 + (16 * jb + 4 * q + lg) * HD + 16 * kb + li];
-#pragma unroll
-            for (int sb = 0; sb < 4; ++sb)
-              dh4[sb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa, slA[(16 * sb + li) * 16 + 4 * q + lg], dh4[sb], 0, 0,
-                                                             0);
+            for (int r = 0; r < 4; ++r) atomicAdd(gr + Sh::oW2 + (16 * o + 4 * r + lg) * HD + 16 * k + ui, w2[r]);
           }
+          const f4v w = w_col(Sh::oW2, 16 * o + 4 * lg, HD, 16 * k + li);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) t[q] = mfma16(w, a2[o][q], t[q]);
           wave_sync();
-          __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int sb = 0; sb < 4; ++sb) *(f4v*)(slB + (16 * sb + li) * 16 + 4 * lg) = dh4[sb];
-        wave_sync();
-        {
-          const f4v* own = (const f4v*)(slB + lane * 16);
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f4v dq = own[q];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) a1b[4 * q + e] = dq[e] * gelu_grad(a1b[4 * q + e]);   // now g1
-          }
-        }
-        slab_store(slA, lane, a1b);
+          for (int r = 0; r < 4; ++r)
+            // (h = 16 has always had the fused form, h = 64 the other)
+            t[q][r] *= gelu_grad<HD == 16>(a1[k][q][r]);   // now g1
+        slab_store(slA, lane, t);
+        slab_store(slB, lane, xq);
         wave_sync();
         if constexpr (kChain) {
-          cw1 = slab_outer(slA, slC, lane, cw1);
+          cw1 = slab_outer(slA, slB, lane, cw1);
           cb1 = slab_sum(slA, lane, cb1);
         } else {
-          const f4v w1 = slab_outer(slA, slC, lane);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) atomicAdd(gm + Sh::oW1 + (16 * kb + 4 * lg + r) * 16 + li, w1[r]);
           const f4v b1 = slab_sum(slA, lane);
           if (li == 0) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) atomicAdd(gm + Sh::oB1 + 16 * kb + 4 * lg + r, b1[r]);
+            for (int r = 0; r < 4; ++r) atomicAdd(gr + Sh::oB1 + 16 * k + 4 * r + lg, b1[r]);
           }
-        }
+          const f4v w1 = slab_outer(slA, slB, lane);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float wa = sw[Sh::oW1 + (16 * kb + 4 * q + lg) * 16 + li];
-#pragma unroll
-          for (int sb = 0; sb < 4; ++sb)
-            dx4[sb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa, slA[(16 * sb + li) * 16 + 4 * q + lg], dx4[sb], 0, 0, 0);
+          for (int r = 0; r < 4; ++r) atomicAdd(gr + Sh::oW1 + (16 * k + 4 * r + lg) * 16 + ui, w1[r]);
         }
-        wave_sync();
-        __builtin_amdgcn_sched_barrier(0);
+        const f4v w = w_col(Sh::oW1, 16 * k + 4 * lg, 16, li);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) dxq[q] = mfma16(w, t[q], dxq[q]);
+        wave_sync();   // the slabs may be staged again
       }
-#pragma unroll
-      for (int sb = 0; sb < 4; ++sb) *(f4v*)(slB + (16 * sb + li) * 16 + 4 * lg) = dx4[sb];
-      wave_sync();
-      float dx[16];
+      float dx[16];   // back to the samples' lanes
       {
-        const f4v* own = (const f4v*)(slB + lane * 16);
+        float t4[4][4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f4v dq = own[q];
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) dx[4 * q + e] = dq[e];
-        }
+          for (int r = 0; r < 4; ++r) t4[q][r] = dxq[q][r];
+        transpose_rows(t4);
+#pragma unroll
+        for (int c = 0; c < 16; ++c) dx[c] = t4[c & 3][c >> 2];
       }
-      wave_sync();   // every lane holds its dx: the slabs take the scatter staging below
       // The taps again, recomputed from the sample's texel and time rather than kept through
       // the decoder backward (the empty asm hides that they equal the forward's, so they are
       // not reused from it).
@@ -504,47 +630,49 @@ __global__ __launch_bounds__(kHtMaxThreads) void k_hybrid_train(HybTrainDims d, 
       float taur = tau;
       asm volatile("" : "+v"(xr), "+v"(yr), "+v"(taur));
       const SampleTaps T = sample_taps(d, xr, yr, taur);
-      const NodeT &ns = T.ns, &nk = T.nk;
-      const float* tw = T.tw;
-      const int *txs = T.txs, *tys = T.tys;
-      const int64_t fpu = T.fpu;
-      const Axis &pu = T.pu, &pv = T.pv;
+      TexRaw<SIM> raw[2][4];
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) raw[sl][i] = tex_load<SIM>(P + d.o_tep + 8 * T.fp[sl][i], P + d.o_tw + T.wi[sl][i]);
+      const TexRaw<SIM> ru = tex_load<SIM>(P + 8 * T.fpu, P + d.o_uvw + T.wu);
       // ---- feature gradients (straight-through for the simulated maps).  Adds into HBM go
       // through the wave's slabs in runs of consecutive words (ht_scatter), so that an
       // instruction covers whole runs of a few samples; adds into the chunk's LDS
       // accumulators are issued per lane.  Dead lanes stage skipped runs.
       float* const sv = slA;          // staged values [64][R x L] (slabs A and B)
-      int* const so = (int*)slC;      // staged run offsets into G [64][R]; negative skips
+      int* const so = (int*)(slB + kSlab);   // staged run offsets into G [64][R]; negative skips
       // Per F_uvt slice the four taps' endpoint terms are first summed per 4x4 footprint (taps
       // 0/1 and 2/3 share one when their columns do, taps 0/2 and 1/3 when their rows do), so
       // each footprint the sample touches takes one set of 8 adds.
-      const bool fsx = (txs[0] >> 2) == (txs[1] >> 2), fsy = (tys[0] >> 2) == (tys[2] >> 2);
+      const bool fsx = (T.gx.i0 >> 2) == (T.gx.i1 >> 2), fsy = (T.gy.i0 >> 2) == (T.gy.i1 >> 2);
 #pragma unroll
       for (int sl = 0; sl < 2; ++sl) {
-        const int si = sl ? ns.i1 : ns.i0;
-        const float ws = sl ? ns.w1 : ns.w0;
+        const float ws = sl ? T.ns.w1 : T.ns.w0;
         float e[4][8];
-        int64_t fps[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int64_t fp = ((int64_t)si * (d.Gv / 4) + (tys[i] >> 2)) * (d.Gu / 4) + (txs[i] >> 2);
-          const int64_t wi = (((int64_t)si * d.Gv + tys[i]) * d.Gu + txs[i]) * d.cw;
-          const BcTex b = sim_texel(P + d.o_tep + fp * 8, P + d.o_tw + wi, bcsim, direct, d.codec);
-          const float wt = ws * tw[i];
-          fps[i] = fp;
+          const BcTex b = sim_texel<SIM>(raw[sl][i]);
+          const float wt = ws * T.tw[i];
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             const float dv = wt * dx[c];
             e[i][2 * c] = dv * b.d1[c];
             e[i][2 * c + 1] = dv * b.d2[c];
-            if (!d.codec) sv[lane * 16 + 4 * i + c] = dv * b.dw[c];
+            if constexpr (!bc7) sv[lane * 16 + 4 * i + c] = dv * b.dw[c];
           }
-          if (d.codec) sv[lane * 4 + i] = wt * (dx[0] * b.dw[0] + dx[1] * b.dw[1] + dx[2] * b.dw[2] + dx[3] * b.dw[3]);
-          so[lane * 4 + i] = live ? (int)(d.o_tw + wi) : -1;
+          if constexpr (bc7) {
+            const float dw = wt * fmaf(dx[3], b.dw[3], fmaf(dx[2], b.dw[2], fmaf(dx[1], b.dw[1], dx[0] * b.dw[0])));
+            if (nW) {
+              if (live) atomicAdd(acc + oW + T.wi[sl][i], dw);   // LDS
+            } else {
+              sv[lane * 4 + i] = dw;
+            }
+          }
+          so[lane * 4 + i] = live ? (int)d.o_tw + T.wi[sl][i] : -1;
         }
-        if (d.codec) ht_scatter<4, 1>(G, sv, so, lane);
-        else ht_scatter<4, 4>(G, sv, so, lane);
-        if (direct) continue;   // a directly optimised map has no endpoints
+        if (!bc7 || !nW) ht_scatter<4, bc7 ? 1 : 4>(G, sv, so, lane);
+        if constexpr (direct) continue;   // a directly optimised map has no endpoints
         if (fsx) {
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
@@ -565,94 +693,100 @@ __global__ __launch_bounds__(kHtMaxThreads) void k_hybrid_train(HybTrainDims d, 
           if (accum) {
             if (own) {
 #pragma unroll
-              for (int k = 0; k < 8; ++k) atomicAdd(acc + fps[i] * 8 + k, e[i][k]);   // LDS (ds_add)
+              for (int k = 0; k < 8; ++k) atomicAdd(acc + k * sF + T.fp[sl][i], e[i][k]);   // LDS (ds_add)
             }
           } else {
 #pragma unroll
             for (int k = 0; k < 8; ++k) sv[lane * 32 + 8 * i + k] = e[i][k];
-            so[lane * 4 + i] = own ? (int)(d.o_tep + fps[i] * 8) : -1;
+            so[lane * 4 + i] = own ? (int)d.o_tep + 8 * T.fp[sl][i] : -1;
           }
         }
         if (!accum) ht_scatter<4, 8>(G, sv, so, lane);
       }
-      // F_uv's texel again (recomputed rather than kept through the decoder backward)
-      const BcTex bu = sim_texel(P + fpu * 8, P + d.o_uvw + ((int64_t)y * d.W + x) * d.cw, bcsim, direct, d.codec);
-      if (!direct) {
+      const BcTex bu = sim_texel<SIM>(ru);
+      if constexpr (!direct) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           sv[lane * 8 + 2 * c] = dx[4 + c] * bu.d1[c];
           sv[lane * 8 + 2 * c + 1] = dx[4 + c] * bu.d2[c];
         }
-        so[lane] = live ? (int)(fpu * 8) : -1;
+        so[lane] = live ? 8 * T.fpu : -1;
         ht_scatter<1, 8>(G, sv, so, lane);
       }
-      if (!d.codec) {
+      if constexpr (!bc7) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) sv[lane * 4 + c] = dx[4 + c] * bu.dw[c];
-        so[lane] = live ? (int)(d.o_uvw + ((int64_t)y * d.W + x) * 4) : -1;
+        so[lane] = live ? (int)d.o_uvw + T.wu : -1;
         ht_scatter<1, 4>(G, sv, so, lane);
       } else if (live) {
-        atomicAdd(G + d.o_uvw + (int64_t)y * d.W + x,
-                  dx[4] * bu.dw[0] + dx[5] * bu.dw[1] + dx[6] * bu.dw[2] + dx[7] * bu.dw[3]);
+        atomicAdd(G + d.o_uvw + T.wu, fmaf(dx[7], bu.dw[3], fmaf(dx[6], bu.dw[2], fmaf(dx[5], bu.dw[1], dx[4] * bu.dw[0]))));
       }
 #pragma unroll
       for (int pl = 0; pl < 2; ++pl) {
-        const int64_t off = pl ? d.o_vt : d.o_ut;
-        const int size = pl ? d.V : d.U;
-        const Axis& a = pl ? pv : pu;
+        const Axis& a = pl ? T.pv : T.pu;
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
           for (int aa = 0; aa < 2; ++aa) {
-            const float w = (kk ? nk.w1 : nk.w0) * (aa ? a.w1 : a.w0);
-            const int64_t idx = off + ((int64_t)(kk ? nk.i1 : nk.i0) * size + (aa ? a.i1 : a.i0)) * 2;
+            const float w = (kk ? T.nk.w1 : T.nk.w0) * (aa ? a.w1 : a.w0);
+            // texel of the two planes side by side
+            const int at = (pl ? d.Tt * d.U : 0) + (kk ? T.nk.i1 : T.nk.i0) * (pl ? d.V : d.U) + (aa ? a.i1 : a.i0);
             const int tap = 4 * pl + 2 * kk + aa;
             if (accum) {
               if (live) {
-                atomicAdd(acc + nE + (idx - d.o_ut), w * dx[8 + 2 * pl]);
-                atomicAdd(acc + nE + (idx - d.o_ut) + 1, w * dx[9 + 2 * pl]);
+                atomicAdd(acc + oP + at, w * dx[8 + 2 * pl]);
+                atomicAdd(acc + oP + nT + at, w * dx[9 + 2 * pl]);
               }
             } else {
               sv[lane * 16 + 2 * tap] = w * dx[8 + 2 * pl];
               sv[lane * 16 + 2 * tap + 1] = w * dx[9 + 2 * pl];
-              so[lane * 8 + tap] = live ? (int)idx : -1;
+              so[lane * 8 + tap] = live ? (int)d.o_ut + 2 * at : -1;
             }
           }
       }
       if (!accum) ht_scatter<8, 2>(G, sv, so, lane);
     }
   }
-    if constexpr (kChain && MODE != NDGI_TRAIN_FORWARD) {   // the chunk's decoder sums into HBM
-      if (lg == 0) {
+    if constexpr (MODE != NDGI_TRAIN_FORWARD) {   // the chunk's decoder sums into HBM
+      if constexpr (kChain) {
+        if (lg == 0) {
 #pragma unroll
-        for (int r = 0; r < 3; ++r) atomicAdd(gm + Sh::oW3 + r * HD + li, cw3[r]);
-      }
-      if (lane == 0) {
-#pragma unroll
-        for (int r = 0; r < 3; ++r) atomicAdd(gm + Sh::oB3 + r, cb3[r]);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        atomicAdd(gm + Sh::oW2 + (4 * lg + r) * HD + li, cw2[r]);
-        atomicAdd(gm + Sh::oW1 + (4 * lg + r) * 16 + li, cw1[r]);
-      }
-      if (li == 0) {
+          for (int r = 0; r < 3; ++r) atomicAdd(gm + Sh::oW3 + r * HD + ui, cw3[r]);
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          atomicAdd(gm + Sh::oB2 + 4 * lg + r, cb2[r]);
-          atomicAdd(gm + Sh::oB1 + 4 * lg + r, cb1[r]);
+          atomicAdd(gm + Sh::oW2 + (4 * r + lg) * HD + ui, cw2[r]);
+          atomicAdd(gm + Sh::oW1 + (4 * r + lg) * 16 + ui, cw1[r]);
+        }
+        if (li == 0) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            atomicAdd(gm + Sh::oB1 + 4 * r + lg, cb1[r]);
+            atomicAdd(gm + Sh::oB2 + 4 * r + lg, cb2[r]);
+          }
+        }
+        if (lane == 0) {
+#pragma unroll
+          for (int r = 0; r < 3; ++r) atomicAdd(gm + Sh::oB3 + r, cb3[r]);
         }
       }
+      // one FP64 atomic a wave and chunk: the adds of all waves meet at one address
+      loss = wave_sum_d(loss);
+      if (lane == 0) atomicAdd(loss_acc, loss * loss_w);
     }
     if (accum) {   // the chunk's sums into HBM
       __syncthreads();
-      for (int64_t i = threadIdx.x; i < nE; i += nthr) {
-        const float v = acc[i];
+      for (int i = threadIdx.x; i < 8 * nF; i += nthr) {
+        const float v = acc[(i & 7) * sF + (i >> 3)];
         if (v != 0.0f) atomicAdd(G + d.o_tep + i, v);
       }
-      for (int64_t i = threadIdx.x; i < nP; i += nthr) {
-        const float v = acc[nE + i];
+      for (int i = threadIdx.x; i < 2 * nT; i += nthr) {
+        const float v = acc[oP + (i & 1) * nT + (i >> 1)];
         if (v != 0.0f) atomicAdd(G + d.o_ut + i, v);
+      }
+      for (int i = threadIdx.x; i < nW; i += nthr) {
+        const float v = acc[oW + i];
+        if (v != 0.0f) atomicAdd(G + d.o_tw + i, v);
       }
     }
   }
@@ -937,28 +1071,44 @@ int ndgi_hybrid_train_step(ndgi_ctx* c, ndgi_hybrid_train_state* st, const ndgi_
     int64_t wgs = (b->n + chunk - 1) / chunk;
     const int64_t cap = (int64_t)c->n_cu * 8;
     if (wgs > cap) wgs = cap;
-    const int64_t nE = (int64_t)d.S * (d.Gv / 4) * (d.Gu / 4) * 8, nP = d.o_mlp - d.o_ut;
-    const size_t slab_bytes = (size_t)(nthr / 64) * kSlabsPerWave * kSlab * sizeof(float);
+    const int64_t nE = ((int64_t)d.S * (d.Gv / 4) * (d.Gu / 4) + 8) * 8, nP = d.o_mlp - d.o_ut;
+    const size_t slab_bytes = (size_t)(nthr / 64) * kWaveLds * sizeof(float);
     const size_t acc_bytes = (size_t)(nE + nP) * sizeof(float);
     const size_t sw_bytes = ((size_t)ndgi_hybrid_mlp_size(d.hidden) * sizeof(float) + 15) / 16 * 16;   // static LDS
     int lds_max = 0;
     NDGI_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device));
     // LDS sums pay off when a chunk has several waves' samples or models share the launch
-    const int accum = mode != NDGI_TRAIN_FORWARD && (nthr > 64 || dl.M > 1) && (int64_t)acc_bytes <= kAccMaxBytes &&
-                      sw_bytes + slab_bytes + acc_bytes <= (size_t)lds_max;
-    const size_t dyn_bytes = slab_bytes + (accum ? acc_bytes : 0);
+    const size_t accw_bytes = d.codec == NDGI_CODEC_BC7 ? (size_t)(d.o_ut - d.o_tw) * sizeof(float) : (size_t)lds_max;
+    int accum = mode != NDGI_TRAIN_FORWARD && (nthr > 64 || dl.M > 1) && (int64_t)acc_bytes <= kAccMaxBytes &&
+                sw_bytes + slab_bytes + acc_bytes <= (size_t)lds_max;
+    // F_uvt's weights as well where they fit (BC7, one word a texel): eight adds a sample that each
+    // would touch a segment of their own
+    if (accum && nthr > 64 && sw_bytes + slab_bytes + acc_bytes + accw_bytes <= (size_t)lds_max) accum = 2;
+    const size_t dyn_bytes = slab_bytes + (accum ? acc_bytes : 0) + (accum > 1 ? accw_bytes : 0);
     if (mode != NDGI_TRAIN_FORWARD) hipLaunchKernelGGL(k_zero_d, dim3(1), dim3(64), 0, s, loss_dev, 1);
-#define NDGI_HT(HD, M)                                                                                          \
-  hipLaunchKernelGGL((k_hybrid_train<HD, M>), dim3((unsigned)wgs), dim3(nthr), dyn_bytes, s, dl, st->params,      \
+#define NDGI_HT(HD, M, SIM)                                                                                     \
+  hipLaunchKernelGGL((k_hybrid_train<HD, M, SIM>), dim3((unsigned)wgs), dim3(nthr), dyn_bytes, s, dl, st->params, \
                      st->grads, st->keys, b->samples, b->n, b->target, b->pred, flags, base, inv3n, loss_w, loss_dev, chunk, \
                      accum)
+#define NDGI_HT_SIM(HD, M)                                           \
+  do {                                                               \
+    if (sim == kSimBc4) NDGI_HT(HD, M, kSimBc4);                     \
+    else if (sim == kSimBc4Rounded) NDGI_HT(HD, M, kSimBc4Rounded);  \
+    else if (sim == kSimDirect) NDGI_HT(HD, M, kSimDirect);          \
+    else if (sim == kSimBc7) NDGI_HT(HD, M, kSimBc7);                \
+    else NDGI_HT(HD, M, kSimBc7Rounded);                             \
+  } while (0)
+    const bool rounded = flags & NDGI_HTRAIN_BCSIM;
+    const int sim = d.codec == NDGI_CODEC_BC7 ? (rounded ? kSimBc7Rounded : kSimBc7)
+                                              : ((flags & NDGI_HTRAIN_DIRECT) ? kSimDirect : (rounded ? kSimBc4Rounded : kSimBc4));
     if (mode == NDGI_TRAIN_FORWARD) {
-      if (d.hidden == 16) NDGI_HT(16, NDGI_TRAIN_FORWARD);
-      else NDGI_HT(64, NDGI_TRAIN_FORWARD);
+      if (d.hidden == 16) NDGI_HT_SIM(16, NDGI_TRAIN_FORWARD);
+      else NDGI_HT_SIM(64, NDGI_TRAIN_FORWARD);
     } else {
-      if (d.hidden == 16) NDGI_HT(16, NDGI_TRAIN_LOSS_GRAD);
-      else NDGI_HT(64, NDGI_TRAIN_LOSS_GRAD);
+      if (d.hidden == 16) NDGI_HT_SIM(16, NDGI_TRAIN_LOSS_GRAD);
+      else NDGI_HT_SIM(64, NDGI_TRAIN_LOSS_GRAD);
     }
+#undef NDGI_HT_SIM
 #undef NDGI_HT
     NDGI_HIP(hipGetLastError());
   }

@@ -341,6 +341,39 @@ def test_production_size_multi_model_batch_matches_oracle(N, ctx, codec):
     assert abs(loss - ref_loss) <= 1e-5 * abs(ref_loss), (loss, ref_loss)
 
 
+@pytest.mark.parametrize("codec,sizes", [
+    (1, (100, 60, 36, 20, 5, 37, 53, 7)),    # F_uvt's endpoints, weights and the planes summed in LDS
+    (0, (100, 60, 36, 20, 5, 37, 53, 7)),    # four weights a texel: endpoints and planes only
+    (1, (92, 68, 64, 64, 5, 31, 5, 2)),      # one weight a texel, which no longer fit
+    (1, (92, 68, 64, 64, 9, 92, 68, 3)),     # the endpoints no longer fit either
+])
+def test_every_gradient_sum_at_ragged_sizes_matches_oracle(N, ctx, codec, sizes):
+    """Grids, planes and maps whose sizes do not divide each other (every interpolation weight
+    a different one), at both sides of the sizes up to which gradients are summed in LDS; a
+    partial last chunk.  Tolerances as for the other batches of this size."""
+    from paper_2604_12625_amd.train import HybridTrainer
+    W, H, Gu, Gv, S, U, V, Tt = sizes
+    st = _state(16, seed=170 + codec, frames=6, codec=codec)
+    g = np.random.default_rng(171)
+    f32 = lambda *shape: g.uniform(0, 1, shape).astype(np.float32).astype(np.float64)
+    st["dims"] = dict(st["dims"], W=W, H=H, Gu=Gu, Gv=Gv, S=S, U=U, V=V, Tt=Tt)
+    cw = () if codec else (4,)
+    st.update(fuv_ep=f32(H // 4, W // 4, 4, 2), fuv_w=f32(H, W, *cw), fuvt_ep=f32(S, Gv // 4, Gu // 4, 4, 2),
+              fuvt_w=f32(S, Gv, Gu, *cw), fut=f32(Tt, U, 2), fvt=f32(Tt, V, 2))
+    x, y, f, tgt = _samples(st, 16700, seed=172)
+    smp, tg = _dev(N, x, y, f, tgt)
+    tr = HybridTrainer(ctx, st, seed=31)
+    pred = tr.forward(smp, 0).cpu().numpy()
+    _close(pred, O.hybrid_train_forward(st, x, y, f, 0, seed=31, step=0), 1e-5, "forward")
+    tr.zero_grad()
+    loss = float(tr.loss_grad(smp, tg, 0).item())
+    ref_loss, ref_g = O.hybrid_train_grads(st, x, y, f, tgt[f, y, x], 0, seed=31, step=0)
+    assert abs(loss - ref_loss) <= 1e-5 * abs(ref_loss), (loss, ref_loss)
+    got = tr.split(tr.grads)
+    for k in O.HYB_KEYS:
+        _close(got[k].cpu().numpy(), ref_g[k], 1e-4, k)
+
+
 @pytest.mark.parametrize("hidden", [16, 64])
 def test_rounds_of_a_chunk_equal_separate_calls(N, ctx, hidden):
     """Eight models x 32768 samples run several 256-sample rounds per chunk (four on a
