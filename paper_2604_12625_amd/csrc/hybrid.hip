@@ -16,9 +16,9 @@
 //  * FP32: v_mfma_f32_16x16x4_f32, step r feeding unit 4g + r of the K block.
 // The weights in that K order (the MFMA A operands) are laid out once per model in an LDS
 // table of 16-byte lane entries: "chunk" = 64 lanes x 16 bytes (8 FP16 slots or 4 FP32
-// steps); the output layer's chunk holds W3 on rows 4k..4k+2 of every row quad k, and group
-// q keeps quad q only, so the 4 groups write rows 4q..4q+2 of one accumulator and after
-// them lane l owns the RGB of texel l of the pass.
+// steps); the output layer's chunk holds W3 on rows 4k..4k+2 of every row quad k, so every lane
+// group ends with the outputs of a group's 16 texels and lane (g, j) keeps group g's: texel l
+// of the pass in lane l.
 #include "hybrid.hpp"
 #include "internal.hpp"
 
@@ -33,9 +33,12 @@ struct HybTab {
 
 // Build the decoder table of a model (all threads of the workgroup; the caller
 // synchronises before use).
-template <int PREC, int HD, int MDT>
+// Every quad of weights starts at a multiple of 4 elements: VEC (the vector is aligned to a quad)
+// loads it at once.
+template <int PREC, int HD, int MDT, bool VEC>
 __device__ void hyb_build_dt(HybTab<HD>& T, const void* mlp) {
   using S = HybShape<HD>;
+  static_assert(S::oW2 % 4 == 0 && S::oW3 % 4 == 0, "quads of weights stay aligned");
   for (int idx = threadIdx.x; idx < S::kChunks * 64; idx += blockDim.x) {
     const int c = idx >> 6, lane = idx & 63, g = lane >> 4, i = lane & 15;
     int base, kbase;   // offset of the row in the packed vector (or -1 for a zero row), first unit
@@ -47,7 +50,7 @@ __device__ void hyb_build_dt(HybTab<HD>& T, const void* mlp) {
       base = S::oW2 + (16 * ob + i) * HD;
       kbase = 16 * kb + 4 * g;
     } else {
-      // output row (i & 3) on every row quad; hyb_group keeps quad q for group q
+      // output row (i & 3) on every row quad
       const int kb = c - S::kL3;
       base = (i & 3) < 3 ? S::oW3 + (i & 3) * HD : -1;
       kbase = 16 * kb + 4 * g;
@@ -55,8 +58,21 @@ __device__ void hyb_build_dt(HybTab<HD>& T, const void* mlp) {
     // loads are unconditional (clamped row), the zero rows select afterwards
     const int row = base < 0 ? S::oW3 : base;
     float w[4];
+    if constexpr (VEC && MDT == NDGI_DTYPE_F16) {
+      typedef _Float16 h4v __attribute__((ext_vector_type(4)));
+      const h4v x = *(const h4v*)((const _Float16*)mlp + row + kbase);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) w[r] = base < 0 ? 0.0f : ld<MDT>(mlp, row + kbase + r);
+      for (int r = 0; r < 4; ++r) w[r] = (float)x[r];
+    } else if constexpr (VEC) {
+      const f4v x = *(const f4v*)((const float*)mlp + row + kbase);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w[r] = x[r];
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w[r] = ld<MDT>(mlp, row + kbase + r);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[r] = base < 0 ? 0.0f : w[r];
     if constexpr (PREC == NDGI_PREC_F16) {
       h8v h;
 #pragma unroll
@@ -75,49 +91,76 @@ __device__ void hyb_build_dt(HybTab<HD>& T, const void* mlp) {
 
 template <int PREC, int HD>
 __device__ void hyb_build(HybTab<HD>& T, const void* mlp, int mlp_dtype) {
-  if (mlp_dtype == NDGI_DTYPE_F16) hyb_build_dt<PREC, HD, NDGI_DTYPE_F16>(T, mlp);
-  else hyb_build_dt<PREC, HD, NDGI_DTYPE_F32>(T, mlp);
+  const bool f16 = mlp_dtype == NDGI_DTYPE_F16, vec = ((uintptr_t)mlp & (f16 ? 7u : 15u)) == 0;
+  if (f16 && vec) hyb_build_dt<PREC, HD, NDGI_DTYPE_F16, true>(T, mlp);
+  else if (f16) hyb_build_dt<PREC, HD, NDGI_DTYPE_F16, false>(T, mlp);
+  else if (vec) hyb_build_dt<PREC, HD, NDGI_DTYPE_F32, true>(T, mlp);
+  else hyb_build_dt<PREC, HD, NDGI_DTYPE_F32, false>(T, mlp);
 }
 
+// A lane's operands of the decoder: read from the table where they are used, or (h = 16: three
+// chunks and two bias quads) held in registers by the caller over its texels.
+template <int HD>
+struct HybOps {
+  const HybTab<HD>* t;
+  int lane;
+  __device__ __forceinline__ void load(const HybTab<HD>& T, int l) { t = &T, lane = l; }
+  __device__ __forceinline__ u4v a(int c) const { return t->a[c * 64 + lane]; }
+  __device__ __forceinline__ f4v b1(int k) const { return *(const f4v*)&t->b1[16 * k + 4 * (lane >> 4)]; }
+  __device__ __forceinline__ f4v b2(int k) const { return *(const f4v*)&t->b2[16 * k + 4 * (lane >> 4)]; }
+  __device__ __forceinline__ f4v b3() const { return *(const f4v*)t->b3; }
+};
+template <>
+struct HybOps<16> {
+  u4v ra[3];
+  f4v rb1, rb2, rb3;
+  __device__ __forceinline__ void load(const HybTab<16>& T, int lane) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) ra[c] = T.a[c * 64 + lane];
+    rb1 = *(const f4v*)&T.b1[4 * (lane >> 4)];
+    rb2 = *(const f4v*)&T.b2[4 * (lane >> 4)];
+    rb3 = *(const f4v*)T.b3;
+  }
+  __device__ __forceinline__ u4v a(int c) const { return ra[c]; }
+  __device__ __forceinline__ f4v b1(int) const { return rb1; }
+  __device__ __forceinline__ f4v b2(int) const { return rb2; }
+  __device__ __forceinline__ f4v b3() const { return rb3; }
+};
+
 // One group of 16 texels through the decoder; x = this lane's K share of layer 1 (inputs
-// 4g..4g+3); the output layer accumulates into acc.
+// 4g..4g+3); lane (g, j) returns the outputs of texel j, whatever g.
 template <int PREC, int HD>
-__device__ __forceinline__ void hyb_group(const HybTab<HD>& T, const float x[4], int q, int lane, f4v& acc) {
+__device__ __forceinline__ f4v hyb_group(const HybOps<HD>& W, const float x[4]) {
   using S = HybShape<HD>;
   constexpr int NB = S::NB;
-  const int g = lane >> 4;
-  const bool own = ((lane & 15) >> 2) == q;   // A rows 4q..4q+2 carry the output layer of group q
+  f4v acc = W.b3();
   if constexpr (PREC == NDGI_PREC_F16) {
-    auto A = [&](int c) { return __builtin_bit_cast(h8v, T.a[c * 64 + lane]); };
+    auto A = [&](int c) { return __builtin_bit_cast(h8v, W.a(c)); };
     const h8v X = split_inputs(x);
     h8v H1[NB], H2[NB];
 #pragma unroll
     for (int mb = 0; mb < NB; ++mb) {
-      const f4v p = __builtin_amdgcn_mfma_f32_16x16x32_f16(A(S::kL1 + mb), X, *(const f4v*)&T.b1[16 * mb + 4 * g],
-                                                           0, 0, 0);
+      const f4v p = __builtin_amdgcn_mfma_f32_16x16x32_f16(A(S::kL1 + mb), X, W.b1(mb), 0, 0, 0);
       const float h[4] = {gelu<PREC>(p[0]), gelu<PREC>(p[1]), gelu<PREC>(p[2]), gelu<PREC>(p[3])};
       H1[mb] = split_inputs(h);
     }
 #pragma unroll
     for (int ob = 0; ob < NB; ++ob) {
-      f4v a = *(const f4v*)&T.b2[16 * ob + 4 * g];
+      f4v a = W.b2(ob);
 #pragma unroll
       for (int kb = 0; kb < NB; ++kb) a = __builtin_amdgcn_mfma_f32_16x16x32_f16(A(S::kL2 + ob * NB + kb), H1[kb], a, 0, 0, 0);
       const float h[4] = {gelu<PREC>(a[0]), gelu<PREC>(a[1]), gelu<PREC>(a[2]), gelu<PREC>(a[3])};
       H2[ob] = split_inputs(h);
     }
 #pragma unroll
-    for (int kb = 0; kb < NB; ++kb) {
-      const h8v a3 = own ? A(S::kL3 + kb) : (h8v){0, 0, 0, 0, 0, 0, 0, 0};
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a3, H2[kb], acc, 0, 0, 0);
-    }
+    for (int kb = 0; kb < NB; ++kb) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(A(S::kL3 + kb), H2[kb], acc, 0, 0, 0);
   } else {
-    auto A = [&](int c) { return __builtin_bit_cast(f4v, T.a[c * 64 + lane]); };
+    auto A = [&](int c) { return __builtin_bit_cast(f4v, W.a(c)); };
     float h1[NB][4], h2[NB][4];
 #pragma unroll
     for (int mb = 0; mb < NB; ++mb) {
       const f4v w = A(S::kL1 + mb);
-      f4v p = *(const f4v*)&T.b1[16 * mb + 4 * g];
+      f4v p = W.b1(mb);
 #pragma unroll
       for (int r = 0; r < 4; ++r) p = __builtin_amdgcn_mfma_f32_16x16x4f32(w[r], x[r], p, 0, 0, 0);
 #pragma unroll
@@ -125,7 +168,7 @@ __device__ __forceinline__ void hyb_group(const HybTab<HD>& T, const float x[4],
     }
 #pragma unroll
     for (int ob = 0; ob < NB; ++ob) {
-      f4v a = *(const f4v*)&T.b2[16 * ob + 4 * g];
+      f4v a = W.b2(ob);
 #pragma unroll
       for (int kb = 0; kb < NB; ++kb) {
         const f4v w = A(S::kL2 + ob * NB + kb);
@@ -137,26 +180,29 @@ __device__ __forceinline__ void hyb_group(const HybTab<HD>& T, const float x[4],
     }
 #pragma unroll
     for (int kb = 0; kb < NB; ++kb) {
-      const f4v w = own ? A(S::kL3 + kb) : (f4v){0.0f, 0.0f, 0.0f, 0.0f};
+      const f4v w = A(S::kL3 + kb);
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[r], h2[kb][r], acc, 0, 0, 0);
     }
   }
+  return acc;
 }
 
 // The decoder over a wave's 64 texels: r[c] holds chunk c of this lane's own texel on
-// entry; returns the output of the lane's texel.
+// entry; returns the output of the lane's texel (lane (g, j) takes group g's).
 template <int PREC, int HD>
-__device__ __forceinline__ f4v hyb_decode(const HybTab<HD>& T, float r[4][4], int lane) {
+__device__ __forceinline__ f4v hyb_decode(const HybOps<HD>& W, float r[4][4], int lane) {
   transpose_rows(r);
-  f4v acc = *(const f4v*)T.b3;
+  f4v o;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    hyb_group<PREC, HD>(T, r[q], q, lane, acc);
+    const f4v z = hyb_group<PREC, HD>(W, r[q]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) o[c] = q == 0 || (lane >> 4) == q ? z[c] : o[c];
     // groups are not interleaved: each one's activations are dead before the next starts
     __builtin_amdgcn_sched_barrier(0);
   }
-  return acc;
+  return o;
 }
 
 // Linear output (no activation); NaN for queries with a non-finite coordinate.
@@ -210,28 +256,17 @@ __device__ __forceinline__ void bc4_fp4(const uint8_t* fp, uint32_t slot, float 
   v[3] = bc4_texel_f(b.z, b.w, slot);
 }
 
-__device__ __forceinline__ void bc4_fp4_regs(const u4v& a, const u4v& b, uint32_t slot, float v[4]) {
-  v[0] = bc4_texel_f(a.x, a.y, slot);
-  v[1] = bc4_texel_f(a.z, a.w, slot);
-  v[2] = bc4_texel_f(b.x, b.y, slot);
-  v[3] = bc4_texel_f(b.z, b.w, slot);
-}
-
 // Bits [pos, pos + n) (n <= 8) of a BC7 block held as a 128-bit little-endian value.
 __device__ __forceinline__ uint32_t bc7_bits(uint64_t lo, uint64_t hi, uint32_t pos, uint32_t n) {
   const uint64_t v = pos >= 64u ? hi >> (pos - 64u) : (pos == 0u ? lo : (lo >> pos) | (hi << (64u - pos)));
   return (uint32_t)v & ((1u << n) - 1u);
 }
-// Index of texel `slot` in an index set of b-bit indices starting at bit pos (texel 0 has
-// b - 1 bits).
-__device__ __forceinline__ uint32_t bc7_index(uint64_t lo, uint64_t hi, uint32_t pos, uint32_t b, uint32_t slot) {
-  return slot ? bc7_bits(lo, hi, pos + b - 1u + b * (slot - 1u), b) : bc7_bits(lo, hi, pos, b - 1u);
-}
 // n-bit endpoint value as 8 bits: the top bits replicated below.
 __device__ __forceinline__ uint32_t bc7_expand(uint32_t v, uint32_t n) { return (v << (8u - n)) | (v >> (2u * n - 8u)); }
 
-// Four channels of texel `slot` of a BC7 block (b = the 16 bytes as a 128-bit little-endian
-// value) in mode 4, 5 or 6, the single-subset modes with four channels; other modes give 0.
+// Texels slot0 .. slot0 + N - 1 (4 channels, channel c in byte c) of a BC7 block (b = the 16
+// bytes as a 128-bit little-endian value) in mode 4, 5 or 6, the single-subset modes with four
+// channels; other modes give 0.
 //  * mode 6 (bits 0..6 = 1000000b): 7-bit endpoint values R0 R1 G0 G1 B0 B1 A0 A1 at bits
 //    7..62, p-bits at 63 and 64, one 4-bit index per texel from bit 65; endpoint (v << 1) | p;
 //  * mode 5 (bits 0..5 = 100000b): rotation at 6..7, 7-bit colour endpoints R0 .. B1 from
@@ -240,67 +275,108 @@ __device__ __forceinline__ uint32_t bc7_expand(uint32_t v, uint32_t n) { return 
 //  * mode 4 (bits 0..4 = 10000b): rotation at 5..6, index selection at 7, 5-bit colour
 //    endpoints from bit 8, 6-bit alpha endpoints at 38 and 44, a 2-bit index set from 50 and
 //    a 3-bit set from 81 (colour takes the 3-bit set when the selection bit is 1).
-// An n-bit endpoint is (v << (8 - n)) | (v >> (2n - 8)); texel ((64 - w) E0 + w E1 + 32) >> 6
-// with w = (64 J + (2^b - 1) / 2) / (2^b - 1), which equals the format's b-bit weight table;
-// rotation r > 0 exchanges channel r - 1 with channel 3 after decoding.
-__device__ __forceinline__ void bc7_fp4_regs(const u4v& b, uint32_t slot, float v[4]) {
+// Texel 0 of a set has one bit less.  An n-bit endpoint is (v << (8 - n)) | (v >> (2n - 8)); texel
+// ((64 - w) E0 + w E1 + 32) >> 6 with w = (64 J + (2^b - 1) / 2) / (2^b - 1), which equals the
+// format's b-bit weight table and is (273 J + 30) >> 6, (585 J + 28) >> 6 and (1365 J + 22) >> 6 for
+// b = 4, 3, 2; rotation r > 0 exchanges channel r - 1 with channel 3 after decoding.
+//
+// The channels go in pairs of 16 bits (64 E0 + 32 + w (E1 - E0) stays below 2^14), so a texel is
+// two packed multiply-adds and shifts and one byte permute, which also rotates.
+typedef uint16_t us2 __attribute__((ext_vector_type(2)));
+template <int N>
+__device__ __forceinline__ void bc7_texels(const u4v& b, uint32_t slot0, uint32_t t[N]) {
   const uint64_t lo = ((uint64_t)b.y << 32) | b.x, hi = ((uint64_t)b.w << 32) | b.z;
-  const uint32_t m = b.x & 0xffu;
-  uint32_t e0[4], e1[4], wc, wa, rot;
-  if ((m & 0x7fu) == 0x40u) {
-    const uint32_t p0 = (uint32_t)(lo >> 63), p1 = (uint32_t)hi & 1u;
-    const uint32_t j = bc7_index(lo, hi, 65u, 4u, slot);
-    wc = wa = (64u * j + 7u) / 15u;
-    rot = 0u;
+  uint32_t e01[2] = {0u, 0u}, e23[2] = {0u, 0u};   // endpoints of channels 0, 1 and 2, 3
+  uint32_t w[N];                                    // colour weight, alpha weight << 16
+  uint32_t sel = 0x06040200u;                       // bytes of the result in (channels 2, 3 : channels 0, 1)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      e0[c] = (bc7_bits(lo, hi, 7u + 14u * c, 7u) << 1) | p0;
-      e1[c] = (bc7_bits(lo, hi, 14u + 14u * c, 7u) << 1) | p1;
+  for (int n = 0; n < N; ++n) w[n] = 0u;
+  const auto rotation = [](uint32_t r) {
+    return r == 0u ? 0x06040200u : (r == 1u ? 0x00040206u : (r == 2u ? 0x02040600u : 0x04060200u));
+  };
+  // n-bit indices of a set whose first has n - 1: all n bits wide
+  const auto widen = [](auto raw, uint32_t n) { return ((raw << 1) & ~(decltype(raw))((1u << n) - 1u)) | (raw & ((1u << (n - 1u)) - 1u)); };
+  if ((b.x & 0x7fu) == 0x40u) {
+    const uint32_t p0 = (b.y >> 31) * 0x10001u, p1 = (b.z & 1u) * 0x10001u;
+    e01[0] = bc7_bits(lo, hi, 7u, 7u) << 1 | bc7_bits(lo, hi, 21u, 7u) << 17 | p0;
+    e01[1] = bc7_bits(lo, hi, 14u, 7u) << 1 | bc7_bits(lo, hi, 28u, 7u) << 17 | p1;
+    e23[0] = bc7_bits(lo, hi, 35u, 7u) << 1 | bc7_bits(lo, hi, 49u, 7u) << 17 | p0;
+    e23[1] = bc7_bits(lo, hi, 42u, 7u) << 1 | bc7_bits(lo, hi, 56u, 7u) << 17 | p1;
+    const uint32_t j0 = (b.z & ~15u) | ((b.z >> 1) & 7u);
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const uint32_t s = slot0 + n, j = (s & 8u ? b.w : j0) >> (4u * (s & 7u)) & 15u;
+      w[n] = ((273u * j + 30u) >> 6) * 0x10001u;
     }
-  } else if ((m & 0x3fu) == 0x20u) {
-    rot = bc7_bits(lo, hi, 6u, 2u);
+  } else if ((b.x & 0x3fu) == 0x20u) {
+    sel = rotation(bc7_bits(lo, hi, 6u, 2u));
+    const auto ex = [&](uint32_t pos) { return bc7_expand(bc7_bits(lo, hi, pos, 7u), 7u); };
+    e01[0] = ex(8u) | ex(22u) << 16;
+    e01[1] = ex(15u) | ex(29u) << 16;
+    e23[0] = ex(36u) | bc7_bits(lo, hi, 50u, 8u) << 16;
+    e23[1] = ex(43u) | bc7_bits(lo, hi, 58u, 8u) << 16;
+    const uint32_t jc = widen((uint32_t)(hi >> 2) & 0x7fffffffu, 2u), ja = widen((uint32_t)(hi >> 33), 2u);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      e0[c] = bc7_expand(bc7_bits(lo, hi, 8u + 14u * c, 7u), 7u);
-      e1[c] = bc7_expand(bc7_bits(lo, hi, 15u + 14u * c, 7u), 7u);
+    for (int n = 0; n < N; ++n) {
+      const uint32_t s = 2u * (slot0 + n);
+      w[n] = (1365u * (jc >> s & 3u) + 22u) >> 6 | ((1365u * (ja >> s & 3u) + 22u) >> 6) << 16;
     }
-    e0[3] = bc7_bits(lo, hi, 50u, 8u);
-    e1[3] = bc7_bits(lo, hi, 58u, 8u);
-    wc = (64u * bc7_index(lo, hi, 66u, 2u, slot) + 1u) / 3u;
-    wa = (64u * bc7_index(lo, hi, 97u, 2u, slot) + 1u) / 3u;
-  } else if ((m & 0x1fu) == 0x10u) {
-    rot = bc7_bits(lo, hi, 5u, 2u);
+  } else if ((b.x & 0x1fu) == 0x10u) {
+    sel = rotation(bc7_bits(lo, hi, 5u, 2u));
+    const auto ex = [&](uint32_t pos, uint32_t n) { return bc7_expand(bc7_bits(lo, hi, pos, n), n); };
+    e01[0] = ex(8u, 5u) | ex(18u, 5u) << 16;
+    e01[1] = ex(13u, 5u) | ex(23u, 5u) << 16;
+    e23[0] = ex(28u, 5u) | ex(38u, 6u) << 16;
+    e23[1] = ex(33u, 5u) | ex(44u, 6u) << 16;
+    const uint32_t j2 = widen((uint32_t)(lo >> 50 | hi << 14) & 0x7fffffffu, 2u);
+    const uint64_t j3 = widen(hi >> 17, 3u);
+    const bool swap = b.x >> 7 & 1u;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      e0[c] = bc7_expand(bc7_bits(lo, hi, 8u + 10u * c, 5u), 5u);
-      e1[c] = bc7_expand(bc7_bits(lo, hi, 13u + 10u * c, 5u), 5u);
+    for (int n = 0; n < N; ++n) {
+      const uint32_t s = slot0 + n;
+      const uint32_t w2 = (1365u * (j2 >> (2u * s) & 3u) + 22u) >> 6, w3 = (585u * ((uint32_t)(j3 >> (3u * s)) & 7u) + 28u) >> 6;
+      w[n] = swap ? w3 | w2 << 16 : w2 | w3 << 16;
     }
-    e0[3] = bc7_expand(bc7_bits(lo, hi, 38u, 6u), 6u);
-    e1[3] = bc7_expand(bc7_bits(lo, hi, 44u, 6u), 6u);
-    const uint32_t w2 = (64u * bc7_index(lo, hi, 50u, 2u, slot) + 1u) / 3u;
-    const uint32_t w3 = (64u * bc7_index(lo, hi, 81u, 3u, slot) + 3u) / 7u;
-    const bool sel = (lo >> 7) & 1u;
-    wc = sel ? w3 : w2;
-    wa = sel ? w2 : w3;
-  } else {
+  }
+  const auto pair = [](uint32_t x) { return __builtin_bit_cast(us2, x); };
+  const us2 a01 = pair(e01[0]) * (uint16_t)64 + (uint16_t)32, a23 = pair(e23[0]) * (uint16_t)64 + (uint16_t)32;
+  const us2 d01 = pair(e01[1]) - pair(e01[0]), d23 = pair(e23[1]) - pair(e23[0]);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) v[c] = 0.0f;
+  for (int n = 0; n < N; ++n) {
+    const us2 wca = pair(w[n]), wcc = {wca.x, wca.x};
+    const us2 t01 = (a01 + d01 * wcc) >> (uint16_t)6, t23 = (a23 + d23 * wca) >> (uint16_t)6;
+    t[n] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, t23), __builtin_bit_cast(uint32_t, t01), sel);
+  }
+}
+__device__ __forceinline__ void bc7_fp4_regs(const u4v& b, uint32_t slot, float v[4]) {
+  uint32_t t[1];
+  bc7_texels<1>(b, slot, t);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) v[c] = (float)(t[0] >> (8 * c) & 0xffu);
+}
+
+// Rows 2h and 2h + 1 of a footprint at fp (BC4 or BC7 as for fp4), channel c of a texel in byte c.
+__device__ __forceinline__ void fp_rows(const uint8_t* fp, int codec, int h, u4v rows[2]) {
+  if (codec) {
+    uint32_t t[8];
+    bc7_texels<8>(*(const u4v*)fp, 8u * (uint32_t)h, t);
+    rows[0] = (u4v){t[0], t[1], t[2], t[3]};
+    rows[1] = (u4v){t[4], t[5], t[6], t[7]};
     return;
   }
-  uint32_t t[4];
+  const u4v a = ((const u4v*)fp)[0], b = ((const u4v*)fp)[1];
+  uint32_t r[4][2];   // four texels of a channel and row
+  bc4_rows(a.x, a.y, h, r[0][0], r[0][1]);
+  bc4_rows(a.z, a.w, h, r[1][0], r[1][1]);
+  bc4_rows(b.x, b.y, h, r[2][0], r[2][1]);
+  bc4_rows(b.z, b.w, h, r[3][0], r[3][1]);
 #pragma unroll
-  for (int c = 0; c < 3; ++c) t[c] = ((64u - wc) * e0[c] + wc * e1[c] + 32u) >> 6;
-  t[3] = ((64u - wa) * e0[3] + wa * e1[3] + 32u) >> 6;
-  if (rot) {
-    const uint32_t r = rot - 1u;
-    const uint32_t x = r == 0u ? t[0] : (r == 1u ? t[1] : t[2]);
-    t[0] = r == 0u ? t[3] : t[0];
-    t[1] = r == 1u ? t[3] : t[1];
-    t[2] = r == 2u ? t[3] : t[2];
-    t[3] = x;
+  for (int k = 0; k < 2; ++k) {
+    const uint32_t p0 = __builtin_amdgcn_perm(r[1][k], r[0][k], 0x05010400u), p1 = __builtin_amdgcn_perm(r[1][k], r[0][k], 0x07030602u);
+    const uint32_t q0 = __builtin_amdgcn_perm(r[3][k], r[2][k], 0x05010400u), q1 = __builtin_amdgcn_perm(r[3][k], r[2][k], 0x07030602u);
+    rows[k] = (u4v){__builtin_amdgcn_perm(q0, p0, 0x05040100u), __builtin_amdgcn_perm(q0, p0, 0x07060302u),
+                    __builtin_amdgcn_perm(q1, p1, 0x05040100u), __builtin_amdgcn_perm(q1, p1, 0x07060302u)};
   }
-#pragma unroll
-  for (int c = 0; c < 4; ++c) v[c] = (float)t[c];
 }
 
 // Four channels (0..255) of texel `slot` of a footprint: 32 bytes of BC4 (codec 0) or one
@@ -319,12 +395,7 @@ __global__ __launch_bounds__(256) void k_bc7_blocks(const uint8_t* __restrict__ 
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       uint32_t w[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        float v[4];
-        bc7_fp4_regs(blk, (uint32_t)(4 * q + k), v);
-        w[k] = (uint32_t)v[0] | (uint32_t)v[1] << 8 | (uint32_t)v[2] << 16 | (uint32_t)v[3] << 24;
-      }
+      bc7_texels<4>(blk, (uint32_t)(4 * q), w);
       ((u4v*)out)[4 * b + q] = (u4v){w[0], w[1], w[2], w[3]};
     }
   }
@@ -403,9 +474,13 @@ __host__ __device__ inline bool hybrid_ok(const ndgi_hybrid_model& m) {
 // ---------------------------------------------------------------------- query decode
 // Grid-stride passes of 64 consecutive queries per wave (one query per lane in the feature
 // phase, the decoder after the handoff); the decoder table and the key table are built
-// once per workgroup in LDS.
+// once per workgroup in LDS.  Bound by vector instructions (about 10 an activation, 18 a
+// BC4 tap and channel) and, for small n, by the table's build.  300007 queries, h = 64, FP16, BC4
+// layout: 43.2 us with the weights loaded one by one and four output accumulators' rows masked
+// in, 35.8 with quads loaded at once and the outputs selected; h = 16, BC7: 18.1 and 17.2.  At
+// most 128 registers (4 waves a SIMD): 154 without the bound, for 12 blocks in flight.
 template <int PREC, int HD, int CD>
-__global__ __launch_bounds__(256) void k_hybrid_query(ndgi_hybrid_model m, const float* __restrict__ uvt, int64_t n,
+__global__ __launch_bounds__(256, 4) void k_hybrid_query(ndgi_hybrid_model m, const float* __restrict__ uvt, int64_t n,
                                                        void* __restrict__ out) {
   __shared__ HybTab<HD> tab;
   __shared__ float keys[NDGI_HYBRID_MAX_KEYS];
@@ -424,7 +499,13 @@ __global__ __launch_bounds__(256) void k_hybrid_query(ndgi_hybrid_model m, const
     const HybTime ht = hyb_time(m, t, [&](int i) { return keys[i]; });
     float r[4][4];
     hyb_query_feats<CD>(m, u, v, ht, r);
-    const f4v acc = hyb_decode<PREC, HD>(tab, r, lane);
+    // the operands are read again for each pass (the empty asm keeps them out of registers while
+    // the features are computed, which need as many)
+    int l = lane;
+    asm volatile("" : "+v"(l));
+    HybOps<HD> ops;
+    ops.load(tab, l);
+    const f4v acc = hyb_decode<PREC, HD>(ops, r, lane);
     if (mine < n) store_lin<PREC>(out, (size_t)mine, acc, bad);
   }
 }
@@ -439,13 +520,19 @@ __global__ __launch_bounds__(256) void k_hybrid_query(ndgi_hybrid_model m, const
 // workgroup stages in LDS:
 //  * the F_uvt nodes the sub-tile reads, decoded from both slices around tau and blended
 //    in time (at most 35 x 35 nodes, since Gu <= W and Gv <= H);
+//  * the F_uv texels of the footprints it touches (at most 10 x 10), each footprint decoded
+//    once (at a texel centre the bilinear weights are 1 and 0);
 //  * per sub-tile column: its F_uvt taps and weight and its V_ut (F_ut blended in time,
 //    then along u); per row: its F_uvt taps and weight and its V_vt;
-// then each pass of a wave decodes 64 consecutive texels of the sub-tile (row-major): the
-// F_uv texel straight from its block (at a texel centre the bilinear weights are 1 and
-// 0), the rest from LDS.  Texel-centre axes use exact integer arithmetic (texel_axis).
+// then each pass of a wave decodes 64 consecutive texels of the sub-tile (row-major) from
+// LDS alone.  Bound by vector instructions: 449 a pass and lane, 340 of them the 32
+// activations (784 with the F_uv block decoded by every texel of it).  64 M-profile BC7 tiles of
+// 136 x 136 texels, FP16: 35.1 us before, 31.5 with the blocks decoded once, the operands of an
+// h = 16 decoder in registers and the table's quads loaded at once; about 8 of them are the launch
+// and the chain request -> model -> table.  5 workgroups a CU spill (34.0).  Texel-centre axes use exact integer arithmetic (texel_axis).
 constexpr int kHybSub = 34;
 constexpr int kHybWin = kHybSub + 1;
+constexpr int kHybBlocks = (kHybSub + 3 + 3) / 4;   // footprints that kHybSub texels can touch along one axis
 
 // Mirror addressing of a texel index on n texels (one reflection: -n <= i < 2n).
 __device__ __forceinline__ int mirror_texel(int i, int n) { return i < 0 ? -1 - i : (i >= n ? 2 * n - 1 - i : i); }
@@ -470,15 +557,16 @@ __device__ __forceinline__ float2 plane_at(const uint16_t* pl, uint32_t size, co
 }
 
 template <int PREC, int HD>
-__global__ __launch_bounds__(256) void k_hybrid_pages(const ndgi_hybrid_model* __restrict__ models, int32_t n_models,
+__global__ __launch_bounds__(256, HD == 16 ? 4 : 3) void k_hybrid_pages(const ndgi_hybrid_model* __restrict__ models, int32_t n_models,
                                                        const ndgi_page_req* __restrict__ reqs,
                                                        const int32_t* __restrict__ n_reqs_dev, int32_t max_reqs,
                                                        int32_t page, void* __restrict__ dst, int64_t pitch,
                                                        int32_t widths, int32_t border, uint32_t* __restrict__ flags) {
   __shared__ HybTab<HD> tab;
   __shared__ f4v win[kHybWin * kHybWin];
+  __shared__ u4v tex[4 * kHybBlocks * kHybBlocks];      // F_uv texels, rows of 4 x (footprints across)
   __shared__ float skeys[NDGI_HYBRID_MAX_KEYS];
-  __shared__ int4 rows_g[kHybSub], cols_g[kHybSub];     // F_uvt window taps and weight
+  __shared__ int4 rows_g[kHybSub], cols_g[kHybSub];     // F_uvt window taps and weight; place in tex
   __shared__ float2 rows_v[kHybSub], cols_u[kHybSub];   // V_vt per row, V_ut per column
   static_assert(NDGI_HYBRID_MAX_KEYS <= 256, "one key per thread");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -528,8 +616,18 @@ __global__ __launch_bounds__(256) void k_hybrid_pages(const ndgi_hybrid_model* _
     const int wx0 = texel_axis<false>(xlo, m.Gu, m.W).i0, wy0 = texel_axis<false>(ylo, m.Gv, m.H).i0;
     const int nwx = min(texel_axis<false>(xhi, m.Gu, m.W).i1 - wx0 + 1, kHybWin);
     const int nwy = min(texel_axis<false>(yhi, m.Gv, m.H).i1 - wy0 + 1, kHybWin);
+    // F_uv footprints of the sub-tile: each is decoded once, half of it a thread
+    const int bx0 = xlo >> 2, by0 = ylo >> 2;
+    const int nbx = min((xhi >> 2) - bx0 + 1, kHybBlocks), nby = min((yhi >> 2) - by0 + 1, kHybBlocks);
+    const uint32_t fpb = m.codec ? 16u : 32u;
+    for (int idx = threadIdx.x; idx < 2 * nbx * nby; idx += 256) {
+      const int h = idx & 1, bk = idx >> 1, by = bk / nbx, bx = bk - by * nbx;
+      u4v rows[2];
+      fp_rows(m.fuv + ((uint32_t)(by0 + by) * ((uint32_t)m.W >> 2) + (uint32_t)(bx0 + bx)) * fpb, m.codec, h, rows);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) tex[(4 * by + 2 * h + k) * nbx + bx] = rows[k];
+    }
     {
-      const uint32_t fpb = m.codec ? 16u : 32u;
       const uint32_t gbw = (uint32_t)m.Gu >> 2, slice = gbw * ((uint32_t)m.Gv >> 2) * fpb;
       const uint8_t* s0 = m.fuvt + (uint32_t)ht.s.i0 * slice;
       const uint8_t* s1 = m.fuvt + (uint32_t)ht.s.i1 * slice;
@@ -553,7 +651,8 @@ __global__ __launch_bounds__(256) void k_hybrid_pages(const ndgi_hybrid_model* _
         const int pos = mirror_texel(isc ? mx0 + i0 + min(k, ni - 1) : my0 + j0 + min(k, nj - 1), n);
         const Axis a = texel_axis<false>(pos, g, n);
         const int o0 = isc ? wx0 : wy0, nn = isc ? nwx : nwy;
-        const int4 e = make_int4(min(max(a.i0 - o0, 0), nn - 1), min(max(a.i1 - o0, 0), nn - 1), __float_as_int(a.w1), 0);
+        const int4 e = make_int4(min(max(a.i0 - o0, 0), nn - 1), min(max(a.i1 - o0, 0), nn - 1), __float_as_int(a.w1),
+                                 isc ? pos - 4 * bx0 : (pos - 4 * by0) * 4 * nbx);
         const float2 pv = plane_at((const uint16_t*)(isc ? m.fut : m.fvt), (uint32_t)pn, texel_axis<false>(pos, pn, n),
                                    ht.k);
         if (isc) {
@@ -566,38 +665,14 @@ __global__ __launch_bounds__(256) void k_hybrid_pages(const ndgi_hybrid_model* _
       }
     }
     __syncthreads();                // table and windows complete
-    const uint32_t fbw = (uint32_t)m.W >> 2;
-    const uint32_t ffb = m.codec ? 16u : 32u;
+    HybOps<HD> ops;
+    ops.load(tab, lane);
     const int nt = ni * nj, passes = (nt + 63) >> 6;
     const uint32_t mag = (65536u + (uint32_t)ni - 1u) / (uint32_t)ni;   // t / ni = (t * mag) >> 16 for t < 2^11
-    // texel of pass p for this lane (row-major in the sub-tile; the tail repeats the last)
-    auto texel_of = [&](int p, int& rj, int& ci) {
-      const int tt = min(p * 64 + lane, nt - 1);
-      rj = (int)(((uint32_t)tt * mag) >> 16);
-      ci = tt - rj * ni;
-    };
-    // its F_uv footprint (one 16-byte BC7 block or 32 bytes of BC4) and texel slot
-    auto footprint = [&](int rj, int ci, uint32_t& slot) {
-      const int x = mirror_texel(mx0 + i0 + ci, m.W), y = mirror_texel(my0 + j0 + rj, m.H);
-      slot = 4u * (uint32_t)(y & 3) + (uint32_t)(x & 3);
-      return (const u4v*)(m.fuv + ((uint32_t)(y >> 2) * fbw + (uint32_t)(x >> 2)) * ffb);
-    };
-    // the F_uv footprint of the next pass is loaded while this one decodes
-    int nr, nc;
-    uint32_t nslot;
-    texel_of(wave, nr, nc);
-    const u4v* nfp = footprint(nr, nc, nslot);
-    u4v fa = nfp[0], fb = m.codec ? fa : nfp[1];
     for (int p = wave; p < passes; p += 4) {
-      const int rj = nr, ci = nc;
-      const uint32_t slot = nslot;
-      const u4v ca = fa, cb = fb;
-      if (p + 4 < passes) {
-        texel_of(p + 4, nr, nc);
-        nfp = footprint(nr, nc, nslot);
-        fa = nfp[0];
-        fb = m.codec ? fa : nfp[1];
-      }
+      // texel of the pass for this lane (row-major in the sub-tile; the tail repeats the last)
+      const int tt = min(p * 64 + lane, nt - 1);
+      const int rj = (int)(((uint32_t)tt * mag) >> 16), ci = tt - rj * ni;
       float rr[4][4];
       // V_uvt: bilinear over the staged nodes
       const int4 ag = rows_g[rj], cg = cols_g[ci];
@@ -608,11 +683,9 @@ __global__ __launch_bounds__(256) void k_hybrid_pages(const ndgi_hybrid_model* _
 #pragma unroll
       for (int c = 0; c < 4; ++c) rr[0][c] = fmaf(w[3], c11[c], fmaf(w[2], c10[c], fmaf(w[1], c01[c], w[0] * c00[c])));
       // V_uv: the texel itself
-      float sv[4];
-      if (m.codec) bc7_fp4_regs(ca, slot, sv);
-      else bc4_fp4_regs(ca, cb, slot, sv);
+      const uint32_t sv = ((const uint32_t*)tex)[ag.w + cg.w];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) rr[1][c] = sv[c] * (1.0f / 255.0f);
+      for (int c = 0; c < 4; ++c) rr[1][c] = (float)(sv >> (8 * c) & 0xffu) * (1.0f / 255.0f);
       // V_ut (per column), V_vt (per row)
       const float2 vut = cols_u[ci], vvt = rows_v[rj];
       rr[2][0] = vut.x;
@@ -621,7 +694,7 @@ __global__ __launch_bounds__(256) void k_hybrid_pages(const ndgi_hybrid_model* _
       rr[2][3] = vvt.y;
 #pragma unroll
       for (int c = 0; c < 4; ++c) rr[3][c] = ht.g[c];
-      const f4v acc = hyb_decode<PREC, HD>(tab, rr, lane);
+      const f4v acc = hyb_decode<PREC, HD>(ops, rr, lane);
       if (p * 64 + lane < nt)
         store_lin<PREC>(dst, (size_t)(rq.dst_offset + (int64_t)(j0 + rj) * pitch + (i0 + ci)), acc, bad_t);
     }

@@ -433,3 +433,66 @@ def test_hybrid_pages_of_any_size(N, ctx, page, border):
     assert valid.sum() == len(reqs) * R * R
     assert_close(out[valid], ref[valid], TOL[1], f"page {page} border {border}")
     np.testing.assert_array_equal(out[~valid], -7.0)
+
+
+@pytest.mark.parametrize("profile", ["M", "M.64"])
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+def test_decoder_weights_at_any_alignment(N, ctx, profile, dtype):
+    """Decoder vectors that start one element past an aligned address (quads of weights then
+    load one by one) give the bits of the aligned ones, for queries and pages."""
+    import torch
+    m = I.random_hybrid_model(64, 64, profile=profile, plane=(32, 32, 8), config=91, uvt_side=(16, 16))
+    hm = N.HybridModel.from_numpy(m)
+    w = torch.from_numpy(m["mlp"]).to("cuda", getattr(torch, dtype))
+    room = torch.zeros(w.numel() + 1, dtype=w.dtype, device="cuda")
+    room[1:] = w
+    d = hm.desc
+    models = [N.HybridModel(d.W, d.H, d.Gu, d.Gv, d.S, d.U, d.V, d.Tt, d.hidden, *hm.arrays[:5], v)
+              for v in (w, room[1:])]
+    assert models[1].desc.mlp % (4 * w.element_size())
+    q = torch.from_numpy(np.random.default_rng(92).random((300, 3)).astype(np.float32)).cuda()
+    rq = N.page_requests(np.zeros(1, np.int32), np.zeros(1, np.int32), np.zeros(1, np.int32),
+                         np.full(1, 0.3, np.float32), np.zeros(1, np.int64))
+    one = torch.ones(1, dtype=torch.int32, device="cuda")
+    for prec in (1, 0):
+        got = []
+        for hm in models:
+            dst = torch.zeros((64 * 64, 3), dtype=(torch.float16 if prec else torch.float32), device="cuda")
+            ctx.hybrid_decode_pages(N.models_array([hm]), 1, rq, one, 1, 64, dst, 64, prec)
+            got.append((ctx.hybrid_decode(hm, q, prec).cpu().numpy(), dst.cpu().numpy()))
+        for a, b in zip(*got):
+            np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("page,border", [(64, 4), (34, 0), (35, 1)])
+def test_pages_of_every_block_mode(N, ctx, page, border):
+    """Random BC7 blocks of modes 4, 5 and 6 (every rotation and index selection) and of modes
+    that decode to 0, in the sub-tiles' staged texels and in F_uvt: pages against the oracle."""
+    import torch
+    g = np.random.default_rng(93)
+    m = I.random_hybrid_model(72, 140, profile="M", plane=(36, 70, 6), config=94, uvt_side=(72, 140), codec=1)
+    for k in ("fuv", "fuvt"):
+        b = g.integers(0, 256, m[k].shape, dtype=np.uint8)
+        mode = g.integers(0, 8, b.shape[:-1])
+        first = b[..., 0]
+        for i, (keep, bit) in enumerate([(0xE0, 0x10), (0xC0, 0x20), (0x80, 0x40)]):
+            sel = (mode < 7) & (mode % 3 == i)
+            first[sel] = (first[sel] & keep) | bit
+        m[k] = b
+    R = page + 2 * border
+    reqs = [(0, px, py, float(np.float32(g.random())), (py * 8 + px) * R) for px in range(72 // page) for py in range(140 // page)]
+    r = np.array(reqs, dtype=object)
+    rq = N.page_requests(r[:, 0].astype(np.int32), r[:, 1].astype(np.int32), r[:, 2].astype(np.int32),
+                         r[:, 3].astype(np.float32), r[:, 4].astype(np.int64))
+    nreq = torch.tensor([len(reqs)], dtype=torch.int32, device="cuda")
+    pitch = 64 * R
+    dst = torch.full((R * pitch, 3), -7.0, dtype=torch.float32, device="cuda")
+    ctx.hybrid_decode_pages(N.models_array([N.HybridModel.from_numpy(m)]), 1, rq, nreq, len(reqs), page, dst, pitch, 0,
+                            border=border)
+    out = dst.cpu().numpy()
+    ref = np.full(out.shape, -7.0)
+    assert O.hybrid_decode_pages([m], reqs, page, ref, pitch, border=border) == 0
+    valid = ref[:, 0] != -7.0
+    assert valid.sum() == len(reqs) * R * R
+    assert_close(out[valid], ref[valid], TOL[0], f"page {page} border {border}")
+    np.testing.assert_array_equal(out[~valid], -7.0)
