@@ -453,6 +453,42 @@ __device__ __forceinline__ h8v texel_x(uint32_t sp, float ga, float gb) {
   return __builtin_bit_cast(h8v, x);
 }
 
+// N (2 or 4) consecutive decoder weights from element i, a multiple of N: at once when the vector
+// is aligned to a quad (VEC), else one by one.  FP16 weights are what gains: a lane's operands
+// are 67 two-byte loads one by one, 19 otherwise, and every wave starts with them.
+template <int MDT, bool VEC, int N>
+__device__ __forceinline__ void ldn(const void* mlp, int i, float v[N]) {
+  if constexpr (VEC && MDT == NDGI_DTYPE_F16) {
+    typedef _Float16 hnv __attribute__((ext_vector_type(N)));
+    const hnv x = *(const hnv*)((const _Float16*)mlp + i);
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = (float)x[k];
+  } else if constexpr (VEC) {
+    typedef float fnv __attribute__((ext_vector_type(N)));
+    const fnv x = *(const fnv*)((const float*)mlp + i);
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = x[k];
+  } else {
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = ld<MDT>(mlp, i + k);
+  }
+}
+// Whether a decoder vector is aligned to a quad of its type.
+__device__ __forceinline__ bool mlp_quads(const void* mlp, int dt) {
+  return ((uintptr_t)mlp & (dt == NDGI_DTYPE_F16 ? 7u : 15u)) == 0;
+}
+// A lane's K shares: inputs input_of(g, 0..3) and units unit_of(g, 0..7) of a weight row at i.
+template <int MDT, bool VEC>
+__device__ __forceinline__ void ld_inputs(const void* mlp, int i, int g, float v[4]) {
+  ldn<MDT, VEC, 2>(mlp, i + input_of(g, 0), v);
+  ldn<MDT, VEC, 2>(mlp, i + input_of(g, 2), v + 2);
+}
+template <int MDT, bool VEC>
+__device__ __forceinline__ void ld_units(const void* mlp, int i, int g, float v[8]) {
+  ldn<MDT, VEC, 4>(mlp, i + unit_of(g, 0), v);
+  ldn<MDT, VEC, 4>(mlp, i + unit_of(g, 4), v + 4);
+}
+
 struct Dec16 {
   h8v a1[2];   // layer 1, rows 16mc + i (see load_dec16 for the K slots)
   h8v a2[2];   // W2 rows 16mo + i, units unit_of(g, 0..7)
@@ -464,17 +500,21 @@ struct Dec16 {
 // weights (they multiply the lo halves).  TEXEL = true: slots 0, 1 take hi(W1/255) of
 // spatial 2g, 2g+1, slots 4, 5 lo(W1/255), slots 2, 3 and 6, 7 the grid weights; c1 has
 // 1024 * sum_s (hi + lo) removed.
-template <int MDT, bool TEXEL>
+template <int MDT, bool TEXEL, bool VEC>
 __device__ __forceinline__ void load_dec16(Dec16& d, const void* mlp, int lane) {
   const int g = lane >> 4, i = lane & 15;
   float off[2] = {0.0f, 0.0f};   // TEXEL: sum over the spatial inputs of unit 16mc + i, in every group
 #pragma unroll
   for (int mc = 0; mc < 2; ++mc) {
     const int u = 16 * mc + i;
+    float w1[4], w2[8], b1[4], b2[4];
+    ld_inputs<MDT, VEC>(mlp, kOffW1 + u * 16, g, w1);
+    ld_units<MDT, VEC>(mlp, kOffW2 + u * 32, g, w2);
+    ldn<MDT, VEC, 4>(mlp, kOffB1 + 16 * mc + 4 * g, b1);
+    ldn<MDT, VEC, 4>(mlp, kOffB2 + 16 * mc + 4 * g, b2);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int in = input_of(g, e & 3);
-      const float w = ld<MDT>(mlp, kOffW1 + u * 16 + in);
+      const float w = w1[e & 3];
       if (TEXEL && (e & 3) < 2) {
         const float ws = w * (1.0f / 255.0f);
         const _Float16 hi = (_Float16)ws;
@@ -484,8 +524,7 @@ __device__ __forceinline__ void load_dec16(Dec16& d, const void* mlp, int lane) 
       }
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      d.a2[mc][e] = (_Float16)ld<MDT>(mlp, kOffW2 + u * 32 + unit_of(g, e));
+    for (int e = 0; e < 8; ++e) d.a2[mc][e] = (_Float16)w2[e];
     if (TEXEL) {   // each group holds two of the eight inputs
       float s = ((float)d.a1[mc][0] + (float)d.a1[mc][4]) + ((float)d.a1[mc][1] + (float)d.a1[mc][5]);
       s += __shfl_xor(s, 16, 64);
@@ -493,18 +532,16 @@ __device__ __forceinline__ void load_dec16(Dec16& d, const void* mlp, int lane) 
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int ur = 16 * mc + 4 * g + r;
-      float b = ld<MDT>(mlp, kOffB1 + ur);
+      float b = b1[r];
       if (TEXEL) b -= 1024.0f * __shfl(off[mc], 4 * g + r, 64);
       d.c1[mc][r] = b;
-      d.c2[mc][r] = ld<MDT>(mlp, kOffB2 + ur);
+      d.c2[mc][r] = b2[r];
     }
   }
   // every load is unconditional (clamped index, then a select): a conditional load would
   // be branched around and serialise the whole set
   float w3[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) w3[e] = ld<MDT>(mlp, kOffW3 + min(i & 3, 2) * 32 + unit_of(g, e));
+  ld_units<MDT, VEC>(mlp, kOffW3 + min(i & 3, 2) * 32, g, w3);
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -545,25 +582,24 @@ struct Dec32 {
   f4v c1[2], c2[2], c3;   // c3: the output bias (the same in every lane)
 };
 
-template <int MDT>
+template <int MDT, bool VEC>
 __device__ __forceinline__ void load_dec32(Dec32& d, const void* mlp, int lane) {
   const int g = lane >> 4, i = lane & 15;
 #pragma unroll
   for (int mc = 0; mc < 2; ++mc) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) d.a1[mc][e] = ld<MDT>(mlp, kOffW1 + (16 * mc + i) * 16 + input_of(g, e));
-#pragma unroll
-    for (int e = 0; e < 8; ++e) d.a2[mc][e] = ld<MDT>(mlp, kOffW2 + (16 * mc + i) * 32 + unit_of(g, e));
+    float b1[4], b2[4];
+    ld_inputs<MDT, VEC>(mlp, kOffW1 + (16 * mc + i) * 16, g, d.a1[mc]);
+    ld_units<MDT, VEC>(mlp, kOffW2 + (16 * mc + i) * 32, g, d.a2[mc]);
+    ldn<MDT, VEC, 4>(mlp, kOffB1 + 16 * mc + 4 * g, b1);
+    ldn<MDT, VEC, 4>(mlp, kOffB2 + 16 * mc + 4 * g, b2);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      d.c1[mc][r] = ld<MDT>(mlp, kOffB1 + 16 * mc + 4 * g + r);
-      d.c2[mc][r] = ld<MDT>(mlp, kOffB2 + 16 * mc + 4 * g + r);
+      d.c1[mc][r] = b1[r];
+      d.c2[mc][r] = b2[r];
     }
   }
 #pragma unroll
-  for (int c = 0; c < 3; ++c)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) d.w3[c][e] = ld<MDT>(mlp, kOffW3 + c * 32 + unit_of(g, e));
+  for (int c = 0; c < 3; ++c) ld_units<MDT, VEC>(mlp, kOffW3 + c * 32, g, d.w3[c]);
 #pragma unroll
   for (int r = 0; r < 4; ++r) d.c3[r] = r < 3 ? ld<MDT>(mlp, kOffB3 + r) : 0.0f;
 }
@@ -609,15 +645,17 @@ template <int PREC> struct Dec;
 template <> struct Dec<NDGI_PREC_F16> {
   Dec16 d;
   typedef f4v Acc;
-  __device__ __forceinline__ void load(const void* mlp, int dt, int lane) {
-    if (dt == NDGI_DTYPE_F16) load_dec16<NDGI_DTYPE_F16, false>(d, mlp, lane);
-    else load_dec16<NDGI_DTYPE_F32, false>(d, mlp, lane);
+  template <bool TEXEL>
+  __device__ __forceinline__ void load_as(const void* mlp, int dt, int lane) {
+    const bool f16 = dt == NDGI_DTYPE_F16, vec = mlp_quads(mlp, dt);
+    if (f16 && vec) load_dec16<NDGI_DTYPE_F16, TEXEL, true>(d, mlp, lane);
+    else if (f16) load_dec16<NDGI_DTYPE_F16, TEXEL, false>(d, mlp, lane);
+    else if (vec) load_dec16<NDGI_DTYPE_F32, TEXEL, true>(d, mlp, lane);
+    else load_dec16<NDGI_DTYPE_F32, TEXEL, false>(d, mlp, lane);
   }
+  __device__ __forceinline__ void load(const void* mlp, int dt, int lane) { load_as<false>(mlp, dt, lane); }
   // weights for texel centres (see load_dec16), used with texel_group
-  __device__ __forceinline__ void load_texel(const void* mlp, int dt, int lane) {
-    if (dt == NDGI_DTYPE_F16) load_dec16<NDGI_DTYPE_F16, true>(d, mlp, lane);
-    else load_dec16<NDGI_DTYPE_F32, true>(d, mlp, lane);
-  }
+  __device__ __forceinline__ void load_texel(const void* mlp, int dt, int lane) { load_as<true>(mlp, dt, lane); }
   __device__ __forceinline__ Acc start() const { return d.c3; }
   __device__ __forceinline__ void group(const float f[4], int q, Acc& acc) const {
     dec16_group(d, split_inputs(f), q, acc);
@@ -633,8 +671,11 @@ template <> struct Dec<NDGI_PREC_F32> {
     float z[4][3];
   };
   __device__ __forceinline__ void load(const void* mlp, int dt, int lane) {
-    if (dt == NDGI_DTYPE_F16) load_dec32<NDGI_DTYPE_F16>(d, mlp, lane);
-    else load_dec32<NDGI_DTYPE_F32>(d, mlp, lane);
+    const bool f16 = dt == NDGI_DTYPE_F16, vec = mlp_quads(mlp, dt);
+    if (f16 && vec) load_dec32<NDGI_DTYPE_F16, true>(d, mlp, lane);
+    else if (f16) load_dec32<NDGI_DTYPE_F16, false>(d, mlp, lane);
+    else if (vec) load_dec32<NDGI_DTYPE_F32, true>(d, mlp, lane);
+    else load_dec32<NDGI_DTYPE_F32, false>(d, mlp, lane);
   }
   __device__ __forceinline__ void load_texel(const void* mlp, int dt, int lane) { load(mlp, dt, lane); }
   __device__ __forceinline__ Acc start() const { return Acc(); }

@@ -104,6 +104,48 @@ def test_decode_ragged_counts(N, ctx, n, prec):
     assert_rel(_dec(N, ctx, m, q, prec), O.decode(m, q), TOL16 if prec else TOL32, f"n={n}")
 
 
+@pytest.mark.parametrize("rounds", [1, 2, 8, 9])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_decode_counts_around_equal_rounds(N, ctx, rounds, prec):
+    """Counts one below, at and one above whole rounds of the resident workgroups (256 queries
+    each): every query gets the bits that it gets in calls of 4096."""
+    import torch
+    m = I.random_model(64, 64, 16, 16, 8, np.float16, np.float16, config=52)
+    dm = N.DeviceModel.from_numpy(m)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    whole = rounds * cus * (2 if prec else 3) * 256
+    q = torch.from_numpy(I.uniform_queries(whole + 1, I.rng(52, I.P_QUERY, rounds))).cuda()
+    ref = torch.cat([ctx.decode(dm, q[i:i + 4096].contiguous(), prec) for i in range(0, whole + 1, 4096)])
+    for n in (whole - 1, whole, whole + 1):
+        assert torch.equal(ctx.decode(dm, q[:n].contiguous(), prec), ref[:n]), n
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+def test_decoder_weights_at_any_alignment(N, ctx, prec, dtype):
+    """Decoder vectors one element past an aligned address (weights then load one by one) give
+    the bits of the aligned ones, for queries and pages."""
+    import torch
+    m = I.random_model(128, 128, 32, 32, 6, np.float16, np.float16, config=53)
+    w = torch.from_numpy(m["mlp"]).to("cuda", getattr(torch, dtype))
+    room = torch.zeros(w.numel() + 1, dtype=w.dtype, device="cuda")
+    room[1:] = w
+    bc4, grid = torch.from_numpy(m["bc4"]).cuda(), torch.from_numpy(m["grid"]).cuda()
+    models = [N.DeviceModel(128, 128, 32, 32, 6, bc4, grid, v) for v in (w, room[1:])]
+    assert models[1].desc.mlp % (4 * w.element_size())
+    q = torch.from_numpy(I.uniform_queries(300, I.rng(53, I.P_QUERY))).cuda()
+    rq = N.page_requests(np.zeros(1, np.int32), np.zeros(1, np.int32), np.zeros(1, np.int32),
+                         np.full(1, 0.3, np.float32), np.zeros(1, np.int64))
+    one = torch.ones(1, dtype=torch.int32, device="cuda")
+    got = []
+    for dm in models:
+        dst = torch.zeros((128 * 128, 3), dtype=(torch.float16 if prec else torch.float32), device="cuda")
+        ctx.decode_pages(N.models_array([dm]), 1, rq, one, 1, 128, dst, 128, prec)
+        got.append((ctx.decode(dm, q, prec).cpu(), dst.cpu()))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
 def test_decode_edges_clamp_wrap_nan(N, ctx):
     m = I.random_model(128, 64, 32, 16, 12, np.float16, np.float16, config=52)
     q = np.array([[-0.5, 0.5, 0.2], [1.7, 0.5, 0.2], [0.5, -3.0, 0.2], [0.5, 9.0, 0.2],
