@@ -85,11 +85,14 @@ int launch_decode(ndgi_ctx* ctx, const ndgi_model& m, const float* uvt, int64_t 
                                 : (const void*)k_decode_query<NDGI_PREC_F32, NDGI_DTYPE_F32>);
   // Waves read from all over the maps, so more of them in flight than hide the latency only evict
   // each other's lines: two workgroups a CU (FP16), three (FP32, whose matrix time needs more to
-  // overlap with).  Few rounds are made equal, so that no round is nearly empty; with many, the last
+  // overlap with, and which a model that lies in the 4 MB L2 of an XCD lets have all).  Few rounds are made equal, so that no round is nearly empty; with many, the last
   // one costs less than the CUs that equal rounds would leave a workgroup short.  FP16, all
   // resident against this: 200k queries 34.4 and 29.6 us, 951k of a 480 x 3620 map 114.6 and
-  // 101.9, 3M of a 256 x 256 map 168 and 147; FP32, 951k: 117 and 104.
-  const int64_t cap = std::min<int64_t>(resident_wgs(ctx, kern), (int64_t)ctx->n_cu * (prec == NDGI_PREC_F16 ? 2 : 3));
+  // 101.9, 3M of a 256 x 256 map 168 and 147; FP32, 951k: 117 and 104; 3M of 1024 x 1024 336 and
+  // 305, of 512 x 512 (3.1 MB) 190 and 197.
+  const int64_t bytes = (int64_t)m.W * m.H * 4 + (int64_t)m.T * m.Gh * m.Gw * (g16 ? 16 : 32);
+  const int per_cu = prec == NDGI_PREC_F16 ? 2 : (bytes > (4 << 20) ? 3 : 8);
+  const int64_t cap = std::min<int64_t>(resident_wgs(ctx, kern), (int64_t)ctx->n_cu * per_cu);
   if (wgs > cap) {
     const int64_t rounds = (wgs + cap - 1) / cap;
     wgs = rounds <= 8 ? (wgs + rounds - 1) / rounds : cap;

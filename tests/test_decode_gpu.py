@@ -105,15 +105,16 @@ def test_decode_ragged_counts(N, ctx, n, prec):
 
 
 @pytest.mark.parametrize("rounds", [1, 2, 8, 9])
-@pytest.mark.parametrize("prec", [0, 1])
-def test_decode_counts_around_equal_rounds(N, ctx, rounds, prec):
-    """Counts one below, at and one above whole rounds of the resident workgroups (256 queries
-    each): every query gets the bits that it gets in calls of 4096."""
+@pytest.mark.parametrize("prec,side", [(0, 64), (0, 1040), (1, 64)])
+def test_decode_counts_around_equal_rounds(N, ctx, rounds, prec, side):
+    """Counts one below, at and one above whole rounds of the workgroups in flight (256 queries
+    each; FP32 at both sides of the model size that its count depends on): every query gets the
+    bits that it gets in calls of 4096."""
     import torch
-    m = I.random_model(64, 64, 16, 16, 8, np.float16, np.float16, config=52)
+    m = I.random_model(side, side, side // 4, side // 4, 8, np.float16, np.float16, config=52)
     dm = N.DeviceModel.from_numpy(m)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    whole = rounds * cus * (2 if prec else 3) * 256
+    whole = rounds * cus * (2 if prec else 4 if side == 64 else 3) * 256
     q = torch.from_numpy(I.uniform_queries(whole + 1, I.rng(52, I.P_QUERY, rounds))).cuda()
     ref = torch.cat([ctx.decode(dm, q[i:i + 4096].contiguous(), prec) for i in range(0, whole + 1, 4096)])
     for n in (whole - 1, whole, whole + 1):
