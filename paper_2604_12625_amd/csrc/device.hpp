@@ -388,9 +388,10 @@ __device__ __forceinline__ void transpose_chunks(const float sp[8], const float 
 // Two layer-1 input forms share the rest of the decoder:
 //  * general (explicit queries): K slots [S_2g, S_2g+1, G_2g, G_2g+1] as hi, then as lo;
 //  * texel centres: the spatial texel is an exact integer, fed as the FP16 value
-//    1024 + u8 (bit pattern 0x6400 | u8) in both halves of K, against the hi and the lo
-//    part of W1/255; the 1024 offset is removed through the bias.  Only the grid inputs
-//    need a hi/lo split.
+//    1 + u8/256 (bit pattern 0x3c00 | u8 << 2) in both halves of K, against the hi and the lo
+//    part of W1 * 256/255; the offset of 1 is removed through the bias.  Only the grid inputs
+//    need a hi/lo split.  (As 1024 + u8 against W1/255 the lo part was subnormal and the weights
+//    kept about 15 bits: an error of up to 5e-5 before the output's rounding, below 2e-6 now.)
 
 // d.lo16 = fp16(v0 - hi.lo16), d.hi16 = fp16(v1 - hi.hi16): the residuals of a packed
 // pair of FP16 values against the FP32 values they came from (one v_fma_mix each).
@@ -446,7 +447,7 @@ __device__ __forceinline__ h8v split_inputs(const float f[4]) {
   return __builtin_bit_cast(h8v, x);
 }
 
-// Layer-1 K share at a texel centre: spatial pair given as 0x6400|u8 halves, grid pair split.
+// Layer-1 K share at a texel centre: spatial pair given as 1 + u8/256 halves, grid pair split.
 __device__ __forceinline__ h8v texel_x(uint32_t sp, float ga, float gb) {
   const uint32_t gh = __builtin_bit_cast(uint32_t, (h2v){(_Float16)ga, (_Float16)gb});
   const u4v x = {sp, gh, sp, resid_pair(gh, ga, gb)};
@@ -497,9 +498,9 @@ struct Dec16 {
 };
 
 // TEXEL = false: layer-1 slots e = 0..3 take W1 at input_of(g, e), slots 4..7 the same
-// weights (they multiply the lo halves).  TEXEL = true: slots 0, 1 take hi(W1/255) of
-// spatial 2g, 2g+1, slots 4, 5 lo(W1/255), slots 2, 3 and 6, 7 the grid weights; c1 has
-// 1024 * sum_s (hi + lo) removed.
+// weights (they multiply the lo halves).  TEXEL = true: slots 0, 1 take hi(W1 * 256/255) of
+// spatial 2g, 2g+1, slots 4, 5 the lo part, slots 2, 3 and 6, 7 the grid weights; c1 has
+// sum_s (hi + lo) removed.  hi stops at the largest FP16 value, which the factor could exceed.
 template <int MDT, bool TEXEL, bool VEC>
 __device__ __forceinline__ void load_dec16(Dec16& d, const void* mlp, int lane) {
   const int g = lane >> 4, i = lane & 15;
@@ -516,8 +517,8 @@ __device__ __forceinline__ void load_dec16(Dec16& d, const void* mlp, int lane) 
     for (int e = 0; e < 8; ++e) {
       const float w = w1[e & 3];
       if (TEXEL && (e & 3) < 2) {
-        const float ws = w * (1.0f / 255.0f);
-        const _Float16 hi = (_Float16)ws;
+        const float ws = w * (256.0f / 255.0f);
+        const _Float16 hi = (_Float16)fminf(fmaxf(ws, -65504.0f), 65504.0f);
         d.a1[mc][e] = e < 4 ? hi : (_Float16)(ws - (float)hi);
       } else {
         d.a1[mc][e] = (_Float16)w;
@@ -533,7 +534,7 @@ __device__ __forceinline__ void load_dec16(Dec16& d, const void* mlp, int lane) 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       float b = b1[r];
-      if (TEXEL) b -= 1024.0f * __shfl(off[mc], 4 * g + r, 64);
+      if (TEXEL) b -= __shfl(off[mc], 4 * g + r, 64);
       d.c1[mc][r] = b;
       d.c2[mc][r] = b2[r];
     }
@@ -661,7 +662,8 @@ template <> struct Dec<NDGI_PREC_F16> {
     dec16_group(d, split_inputs(f), q, acc);
   }
   __device__ __forceinline__ void texel_group(uint32_t sa, uint32_t sb, float ga, float gb, int q, Acc& acc) const {
-    dec16_group(d, texel_x(sa | (sb << 16) | 0x64006400u, ga, gb), q, acc);
+    const uint32_t s = __builtin_amdgcn_perm(sb, sa, 0x0c040c00u);   // sa | sb << 16
+    dec16_group(d, texel_x(s << 2 | 0x3c003c00u, ga, gb), q, acc);
   }
   __device__ __forceinline__ f4v finish(const Acc& acc) const { return acc; }
 };

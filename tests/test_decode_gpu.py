@@ -424,6 +424,29 @@ def test_page_rows_at_every_grid_ratio(N, prec, tol, grid, page, shape):
     c.close()
 
 
+@pytest.mark.parametrize("grid", [(32, 32), (16, 16), (21, 19)])
+@pytest.mark.parametrize("grid_dt", [np.float16, np.float32])
+def test_fp16_pages_round_a_precise_value(N, grid, grid_dt):
+    """FP16 pages hold the FP16 rounding of a value within 8e-6 of the oracle's, relatively: the
+    weights are exact in FP16 and every other operand keeps about 22 bits, which an emulation of the
+    operand pairs in FP32 puts below 2e-6 on He-normal decoders (operands of 15 bits: 5e-5)."""
+    import torch
+    c = N.Context(0)
+    models = [I.random_model(128, 128, grid[0], grid[1], 5, grid_dt, np.float16, config=65, index=i) for i in range(4)]
+    reqs = [(i, 0, 0, np.float32(0.13 + 0.2 * i), i * 128 * 128) for i in range(4)]
+    dms = [N.DeviceModel.from_numpy(m) for m in models]
+    dst = torch.zeros((4 * 128 * 128, 3), dtype=torch.float16, device="cuda")
+    nreq = torch.tensor([4], dtype=torch.int32, device="cuda")
+    c.decode_pages(N.models_array(dms), 4, N.page_requests(*[np.array(v) for v in zip(*reqs)]), nreq, 4, 128, dst, 128,
+                   N.PREC_F16)
+    ref = np.zeros((4 * 128 * 128, 3))
+    assert O.decode_pages(models, reqs, 128, ref, 128) == 0
+    half_ulp = 0.5 * np.spacing(np.minimum(ref * (1 + 8e-6), 65504.0).astype(np.float16)).astype(np.float64)
+    over = np.abs(dst.double().cpu().numpy() - ref) - half_ulp - 8e-6 * ref
+    assert over.max() <= 0, f"{int((over > 0).sum())} values, up to {(over / ref).max():.2e}"
+    c.close()
+
+
 
 @pytest.mark.parametrize("prec,tol", [(1, TOL16), (0, TOL32)])
 def test_pages_many_models_and_bad_requests(N, ctx, prec, tol):
