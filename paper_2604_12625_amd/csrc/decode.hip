@@ -47,9 +47,13 @@ int launch_bc4_blocks(const uint8_t* blocks, int64_t n, uint8_t* out, int impl, 
 // ------------------------------------------------------------------- query decode
 // Each wave takes passes of 64 consecutive queries (phase A: one query per lane; phase B:
 // the decoder after the register handoff); 4 waves per workgroup; grid-stride.
+// FP32 on an FP16 grid is held to three waves a SIMD: for a fourth the compiler gave up the registers
+// in which the grid's eight loads are in flight together, and small calls took 8.3 us instead of 7.4.
 template <int PREC, int GDT>
-__global__ __launch_bounds__(256) void k_decode_query(ndgi_model m, const float* __restrict__ uvt, int64_t n,
-                                                       void* __restrict__ out) {
+constexpr int query_waves() { return PREC == NDGI_PREC_F32 && GDT == NDGI_DTYPE_F16 ? 3 : 8; }
+template <int PREC, int GDT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, query_waves<PREC, GDT>())))
+void k_decode_query(ndgi_model m, const float* __restrict__ uvt, int64_t n, void* __restrict__ out) {
   const int lane = threadIdx.x & 63;
   Dec<PREC> dec;
   dec.load(m.mlp, m.mlp_dtype, lane);
@@ -83,20 +87,30 @@ int launch_decode(ndgi_ctx* ctx, const ndgi_model& m, const float* uvt, int64_t 
                                 : (const void*)k_decode_query<NDGI_PREC_F16, NDGI_DTYPE_F32>)
                          : (g16 ? (const void*)k_decode_query<NDGI_PREC_F32, NDGI_DTYPE_F16>
                                 : (const void*)k_decode_query<NDGI_PREC_F32, NDGI_DTYPE_F32>);
-  // Waves read from all over the maps, so more of them in flight than hide the latency only evict
-  // each other's lines: two workgroups a CU (FP16), three (FP32, whose matrix time needs more to
-  // overlap with, and which a model that lies in the 4 MB L2 of an XCD lets have all).  Few rounds are made equal, so that no round is nearly empty; with many, the last
-  // one costs less than the CUs that equal rounds would leave a workgroup short.  FP16, all
-  // resident against this: 200k queries 34.4 and 29.6 us, 951k of a 480 x 3620 map 114.6 and
-  // 101.9, 3M of a 256 x 256 map 168 and 147; FP32, 951k: 117 and 104; 3M of 1024 x 1024 336 and
-  // 305, of 512 x 512 (3.1 MB) 190 and 197.
-  const int64_t bytes = (int64_t)m.W * m.H * 4 + (int64_t)m.T * m.Gh * m.Gw * (g16 ? 16 : 32);
-  const int per_cu = prec == NDGI_PREC_F16 ? 2 : (bytes > (4 << 20) ? 3 : 8);
-  const int64_t cap = std::min<int64_t>(resident_wgs(ctx, kern), (int64_t)ctx->n_cu * per_cu);
-  if (wgs > cap) {
-    const int64_t rounds = (wgs + cap - 1) / cap;
-    wgs = rounds <= 8 ? (wgs + rounds - 1) / rounds : cap;
+  // Waves read from all over the maps, and more of them in flight than hide the latency only evict
+  // each other's lines: workgroups a CU where all that is resident would be slower (us, all resident
+  // and this):
+  //  * FP16, FP16 grid: 2 (1M queries of 256^2 x 24 60.7 and 54.2, of 1024^2 115 and 103, 16M of
+  //    4096^2 2250 and 1990); a model that lies in the CUs' own caches takes all (3M of 64^2 x 8: 108,
+  //    with two 119).
+  //  * FP16, FP32 grid: 3 (1M of 512^2 98.5 and 92.5), or 2 where the model exceeds the chip's 32 MB
+  //    of L2 and there are rounds to spread over (1M of 1024^2 128 and 114).
+  //  * FP32, FP16 grid: 2 (1M of 4096^2 145 and 133), or 3 for a model within an XCD's L2 and many
+  //    rounds, which is bound by the decoder (3M of 256^2: 176, with two 182).
+  //  * FP32, FP32 grid: 3 (1M of 512^2 102 and 98).
+  // In FP16 up to a quarter of a workgroup a CU beyond that goes with the round: as a round of its own it
+  // would leave the chip idle (131073 queries on an FP32 grid of 512^2: 16.9, cut into two rounds 20.4).
+  const int64_t cu = ctx->n_cu, bytes = (int64_t)m.W * m.H * 4 + (int64_t)m.T * m.Gh * m.Gw * (g16 ? 16 : 32);
+  int64_t per_cu = 3, slack = 0;
+  if (prec == NDGI_PREC_F16) {
+    per_cu = g16 ? (bytes > (128 << 10) ? 2 : 4) : (bytes > (32 << 20) && wgs > 5 * cu ? 2 : 3);
+    slack = cu / 4;
+  } else if (g16) {
+    per_cu = bytes <= (2 << 20) && wgs > 12 * cu ? 3 : 2;
   }
+  const int64_t resident = resident_wgs(ctx, kern);
+  const int64_t cap = wgs > per_cu * cu + slack ? std::min(resident, per_cu * cu) : resident;
+  if (wgs > cap) wgs = cap;
   if (prec == NDGI_PREC_F16 && g16)
     hipLaunchKernelGGL((k_decode_query<NDGI_PREC_F16, NDGI_DTYPE_F16>), dim3((unsigned)wgs), dim3(256), 0, s, m, uvt, n, out);
   else if (prec == NDGI_PREC_F16)

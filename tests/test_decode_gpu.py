@@ -121,6 +121,29 @@ def test_decode_counts_around_equal_rounds(N, ctx, rounds, prec, side):
         assert torch.equal(ctx.decode(dm, q[:n].contiguous(), prec), ref[:n]), n
 
 
+@pytest.mark.parametrize("prec,grid_dt,per_cu", [(1, "float32", 2), (0, "float16", 4), (1, "float16", 4)])
+def test_one_query_more_costs_no_round(N, ctx, prec, grid_dt, per_cu):
+    """A call of one query more than per_cu workgroups a CU takes about as long (1.02 to 1.08 times;
+    1.24 to 1.35 where the workgroups were dealt out anew in more, equal rounds)."""
+    import torch
+    m = I.random_model_torch(512, 512, 128, 128, 24, seed=5, device="cuda", grid_dtype=grid_dt, mlp_dtype="float16")
+    dm = N.DeviceModel(512, 512, 128, 128, 24, m["bc4"], m["grid"], m["mlp"])
+    n = per_cu * 256 * torch.cuda.get_device_properties(0).multi_processor_count
+    q = I.uniform_queries_torch(n + 1, seed=6, device="cuda")
+    out = torch.empty((n + 1, 3), dtype=torch.float16 if prec else torch.float32, device="cuda")
+    best = {}
+    for _ in range(12):
+        for k in (n, n + 1):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(40):
+                ctx.decode(dm, q[:k], prec, out=out)
+            b.record()
+            b.synchronize()
+            best[k] = min(best.get(k, 1e9), a.elapsed_time(b))
+    assert best[n + 1] <= 1.15 * best[n], (1e3 / 40 * best[n], 1e3 / 40 * best[n + 1])
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("dtype", ["float16", "float32"])
 def test_decoder_weights_at_any_alignment(N, ctx, prec, dtype):
