@@ -140,49 +140,138 @@ __device__ __forceinline__ uint32_t bc4_table(int D, int t) {
   return best;
 }
 
-// Bounds and results of one wave's block.
-struct Bc4Wave {
+// Bounds of a block.
+struct Bc4Bounds {
   uint32_t below[256], above[256];   // error of the texels below / above an interval that starts / ends at i
 };
-
-// Every pair of one mode, by difference.  f: two tables of 511 entries, filled by the
-// workgroup one difference ahead of their use.  A lane takes lower endpoint 64 c + lane of
-// chunk c; the texels outside the pair's interval bound its error from below (texel by texel
-// an entry outside the interval is 0 or 255 at best), and a chunk whose bounds all exceed the
-// least error so far is skipped.
+// Texels X (uniform) and, for the 6-value mode, their least squared distance Z to 0 and 255.
 template <bool SIX>
-__device__ __forceinline__ void bc4_pairs(const uint32_t X[16], const uint32_t Z[16], const Bc4Wave& B, uint16_t (&f)[2][512],
-                                          int tid, int lane, bool live, uint32_t& best, uint32_t& pair, uint32_t& lim) {
-#pragma unroll 1
-  for (int D = SIX ? 0 : 1; D < 256; ++D) {
-    uint16_t* const tab = f[D & 1];
-    for (int i = tid; i < 511; i += 256) tab[i] = (uint16_t)bc4_table<SIX>(D, i - 255);
-    __syncthreads();   // filled; and the other table's readers are done
-    if (!live) continue;
-#pragma unroll 1
-    for (int c = 0; 64 * c < 256 - D; ++c) {
-      const int e = 64 * c + lane;
-      const bool in = e + D < 256;
-      const uint32_t bound = B.below[in ? e : 255] + B.above[in ? e + D : 0];
-      if (!__any(in && bound <= lim)) continue;
-      const uint16_t* const at = tab + 255 - (in ? e : 0);
-      uint32_t sse = 0;
+__device__ __forceinline__ void bc4_bound(const uint32_t X[16], const uint32_t Z[16], int v, Bc4Bounds& B) {
+  uint32_t lo = 0, hi = 0;
 #pragma unroll
-      for (int s = 0; s < 16; ++s) {
-        const uint32_t d = at[X[s]];
-        sse += SIX ? min(d, Z[s]) : d;
-      }
-      const uint32_t p = SIX ? (uint32_t)(e * 257 + D) : (uint32_t)(e * 257 + 256 * D);   // e0 * 256 + e1
-      if (in && (sse < best || (sse == best && p < pair))) {
-        best = sse;
-        pair = p;
-      }
-      if (__any(best < lim)) {
-        const uint32_t r = row_min(best);
-        lim = min(min((uint32_t)lane_of((int)r, 0), (uint32_t)lane_of((int)r, 16)),
-                  min((uint32_t)lane_of((int)r, 32), (uint32_t)lane_of((int)r, 48)));
-      }
+  for (int s = 0; s < 16; ++s) {
+    const int d = v - (int)X[s];
+    uint32_t d2 = (uint32_t)(d * d);
+    if (SIX) d2 = min(d2, Z[s]);
+    lo += d > 0 ? d2 : 0u;
+    hi += d < 0 ? d2 : 0u;
+  }
+  B.below[v] = lo;
+  B.above[v] = hi;
+}
+
+__device__ __forceinline__ uint32_t wave_umin(uint32_t v) {
+  const int r = (int)row_min(v);
+  return min(min((uint32_t)lane_of(r, 0), (uint32_t)lane_of(r, 16)), min((uint32_t)lane_of(r, 32), (uint32_t)lane_of(r, 48)));
+}
+
+// A wave's part of difference D of one mode: lane takes lower endpoint 64 c + lane of chunk c;
+// tab: the 511 errors of D.  The texels outside the pair's interval bound its error from below
+// (texel by texel an entry outside the interval is 0 or 255 at best), and a chunk whose bounds
+// all exceed the least error so far (lim) is skipped.
+template <bool SIX>
+__device__ __forceinline__ void bc4_pairs(const uint32_t X[16], const uint32_t Z[16], const Bc4Bounds& B,
+                                          const uint16_t* tab, int D, int lane, uint32_t& best, uint32_t& pair,
+                                          uint32_t& lim) {
+#pragma unroll 1
+  for (int c = 0; 64 * c < 256 - D; ++c) {
+    const int e = 64 * c + lane;
+    const bool in = e + D < 256;
+    const uint32_t bound = B.below[in ? e : 255] + B.above[in ? e + D : 0];
+    if (!__any(in && bound <= lim)) continue;
+    const uint16_t* const at = tab + 255 - (in ? e : 0);
+    uint32_t sse = 0;
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      const uint32_t d = at[X[s]];
+      sse += SIX ? min(d, Z[s]) : d;
     }
+    const uint32_t p = SIX ? (uint32_t)(e * 257 + D) : (uint32_t)(e * 257 + 256 * D);   // e0 * 256 + e1
+    if (in && (sse < best || (sse == best && p < pair))) {
+      best = sse;
+      pair = p;
+    }
+    if (__any(best < lim)) lim = wave_umin(best);
+  }
+}
+
+// Every pair of one mode, by difference.  A wave to a block (PRIV false): f holds two tables,
+// filled by the workgroup one difference ahead of their use.  A workgroup to a block (PRIV): wave
+// w of nw takes every nw-th difference with a table of its own, f[w].
+template <bool SIX, bool PRIV>
+__device__ __forceinline__ void bc4_mode(const uint32_t X[16], const uint32_t Z[16], const Bc4Bounds& B,
+                                         uint16_t (*f)[512], int tid, bool live, int nw, uint32_t& best,
+                                         uint32_t& pair, uint32_t& lim) {
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if constexpr (PRIV) {
+#pragma unroll 1
+    for (int D = (SIX ? 0 : 1) + wave; D < 256; D += nw) {
+      uint16_t* const tab = f[wave];
+      wave_sync();   // the previous difference is read
+      for (int i = lane; i < 511; i += 64) tab[i] = (uint16_t)bc4_table<SIX>(D, i - 255);
+      wave_sync();
+      bc4_pairs<SIX>(X, Z, B, tab, D, lane, best, pair, lim);
+    }
+  } else {
+#pragma unroll 1
+    for (int D = SIX ? 0 : 1; D < 256; ++D) {
+      uint16_t* const tab = f[D & 1];
+      for (int i = tid; i < 511; i += 256) tab[i] = (uint16_t)bc4_table<SIX>(D, i - 255);
+      __syncthreads();   // filled; and the other table's readers are done
+      if (live) bc4_pairs<SIX>(X, Z, B, tab, D, lane, best, pair, lim);
+    }
+  }
+}
+
+// Texel (lane & 15) of block i of the two jobs.
+__device__ __forceinline__ uint32_t bc4_source(const EncodeJob& job, int64_t b, int lane) {
+  if (job.src.u8) return job.src.u8[b * 16 + (lane & 15)];
+  int q[4];
+  src_texel4(job.src, b >> 2, lane & 15, q);
+  const int c = (int)(b & 3);
+  return (uint32_t)(c == 0 ? q[0] : (c == 1 ? q[1] : (c == 2 ? q[2] : q[3])));
+}
+// X and Z, and the least error so far from the texels' own range.
+__device__ __forceinline__ uint32_t bc4_setup(uint32_t x, uint32_t X[16], uint32_t Z[16]) {
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {
+    X[s] = (uint32_t)lane_of((int)x, s);
+    Z[s] = min(X[s] * X[s], (255u - X[s]) * (255u - X[s]));
+  }
+  const uint32_t hi = (uint32_t)lane_of((int)row_max(x), 0), lo = (uint32_t)lane_of((int)row_min(x), 0);
+  const uint32_t e = hi > lo ? bc4_table<false>((int)(hi - lo), (int)x - (int)lo) : 0u;
+  return (uint32_t)lane_of(row_sum((int)e), 0);
+}
+// The wave's least error, then its lowest pair, as one key.
+__device__ __forceinline__ uint64_t bc4_key(uint32_t best, uint32_t pair) {
+  uint64_t key = ((uint64_t)best << 32) | pair;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const uint64_t o = __shfl_xor(key, off, 64);
+    key = o < key ? o : key;
+  }
+  return key;
+}
+// The block of a key's pair; x as above, all lanes of the wave take part.
+__device__ __forceinline__ void bc4_write(uint64_t key, uint32_t x, int lane, uint8_t* out) {
+  const int E0 = (int)((key >> 8) & 255u), E1 = (int)(key & 255u);
+  int p[8];
+  bc4_palette8(E0, E1, p);
+  int code = 0, m = INT_MAX;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const int d = p[c] - (int)x;
+    if (d * d < m) {
+      m = d * d;
+      code = c;
+    }
+  }
+  // gather the 16 selectors and pack
+  uint64_t field = (uint64_t)code << (3 * (lane & 15));
+  field = (uint64_t)row_or((uint32_t)field) | ((uint64_t)row_or((uint32_t)(field >> 32)) << 32);
+  if (lane == 0) {
+    const uint32_t lo = (uint32_t)E0 | ((uint32_t)E1 << 8) | ((uint32_t)(field & 0xffffu) << 16);
+    *(uint2*)out = make_uint2(lo, (uint32_t)(field >> 16));
   }
 }
 
@@ -193,7 +282,7 @@ __device__ __forceinline__ void bc4_pairs(const uint32_t X[16], const uint32_t Z
 // way and take 3.9-5.4 ms.
 __global__ __launch_bounds__(256) void k_encode_bc4(EncodeJob ja, EncodeJob jb) {
   __shared__ uint16_t f[2][512];
-  __shared__ Bc4Wave bounds[4];
+  __shared__ Bc4Bounds bounds[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t n = ja.n + jb.n;
   for (int64_t i0 = 4 * (int64_t)blockIdx.x; i0 < n; i0 += 4 * (int64_t)gridDim.x) {
@@ -201,81 +290,56 @@ __global__ __launch_bounds__(256) void k_encode_bc4(EncodeJob ja, EncodeJob jb) 
     const int64_t i = live ? i0 + wave : n - 1;
     const EncodeJob& job = i < ja.n ? ja : jb;
     const int64_t b = i < ja.n ? i : i - ja.n;
-    uint32_t x;
-    if (job.src.u8) {
-      x = job.src.u8[b * 16 + (lane & 15)];
-    } else {
-      int q[4];
-      src_texel4(job.src, b >> 2, lane & 15, q);
-      const int c = (int)(b & 3);
-      x = (uint32_t)(c == 0 ? q[0] : (c == 1 ? q[1] : (c == 2 ? q[2] : q[3])));
-    }
-    uint32_t X[16], Z[16];   // the texels, and their least squared distance to 0 and 255 (uniform)
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-      X[s] = (uint32_t)lane_of((int)x, s);
-      Z[s] = min(X[s] * X[s], (255u - X[s]) * (255u - X[s]));
-    }
-    Bc4Wave& B = bounds[wave];
-    // the bounds of each mode, and the least error so far from the texels' own range
-    uint32_t best = 0xffffffffu, pair = 0xffffffffu, lim = 0;
-    {
-      const uint32_t hi = (uint32_t)lane_of((int)row_max(x), 0), lo = (uint32_t)lane_of((int)row_min(x), 0);
-      const uint32_t e = hi > lo ? bc4_table<false>((int)(hi - lo), (int)x - (int)lo) : 0u;
-      lim = (uint32_t)lane_of(row_sum((int)e), 0);
-    }
-    auto fill = [&](bool six) {
+    const uint32_t x = bc4_source(job, b, lane);
+    uint32_t X[16], Z[16], best = 0xffffffffu, pair = 0xffffffffu, lim = bc4_setup(x, X, Z);
+    Bc4Bounds& B = bounds[wave];   // private to the wave
+    __syncthreads();               // the previous block's readers of f are done
 #pragma unroll 1
-      for (int k = 0; k < 4; ++k) {
-        const int v = 64 * k + lane;
-        uint32_t lo = 0, hi = 0;
-#pragma unroll
-        for (int s = 0; s < 16; ++s) {
-          const int d = v - (int)X[s];
-          uint32_t d2 = (uint32_t)(d * d);
-          if (six) d2 = min(d2, Z[s]);
-          lo += d > 0 ? d2 : 0u;
-          hi += d < 0 ? d2 : 0u;
-        }
-        B.below[v] = lo;
-        B.above[v] = hi;
-      }
-      wave_sync();   // private to the wave
-    };
-    __syncthreads();   // the previous block's readers of f are done
-    fill(false);
-    bc4_pairs<false>(X, Z, B, f, tid, lane, live, best, pair, lim);
+    for (int k = 0; k < 4; ++k) bc4_bound<false>(X, Z, 64 * k + lane, B);
+    wave_sync();
+    bc4_mode<false, false>(X, Z, B, f, tid, live, 4, best, pair, lim);
     __syncthreads();
-    fill(true);
-    bc4_pairs<true>(X, Z, B, f, tid, lane, live, best, pair, lim);
-    // the least error, then the lowest pair
-    uint64_t key = ((uint64_t)best << 32) | pair;
+#pragma unroll 1
+    for (int k = 0; k < 4; ++k) bc4_bound<true>(X, Z, 64 * k + lane, B);
+    wave_sync();
+    bc4_mode<true, false>(X, Z, B, f, tid, live, 4, best, pair, lim);
+    const uint64_t key = bc4_key(best, pair);
+    if (live) bc4_write(key, x, lane, job.out + b * 8);
+  }
+}
+
+// The same with a workgroup of 16 waves to a block, for launches that would leave most of the chip
+// idle: the differences are dealt out over the waves, which then wait for each other once a block
+// instead of 511 times.  Each wave fills tables that four blocks share above, so many blocks are
+// better off there.  Constant to random texels, above and here: 256 blocks 360-517 and 50-64 us, 2048
+// blocks 430-600 and 375-470, 3000 blocks 500-680 and 555-690.
+constexpr int kBc4OneWaves = 16;
+constexpr int64_t kBc4OnePerCu = 8;   // blocks a CU up to which a workgroup takes one
+__global__ __launch_bounds__(64 * kBc4OneWaves) void k_encode_bc4_one(EncodeJob ja, EncodeJob jb) {
+  __shared__ uint16_t f[kBc4OneWaves][512];
+  __shared__ Bc4Bounds bounds[2];   // of each mode
+  __shared__ uint64_t keys[kBc4OneWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int64_t i = blockIdx.x; i < ja.n + jb.n; i += gridDim.x) {
+    const EncodeJob& job = i < ja.n ? ja : jb;
+    const int64_t b = i < ja.n ? i : i - ja.n;
+    const uint32_t x = bc4_source(job, b, lane);
+    uint32_t X[16], Z[16], best = 0xffffffffu, pair = 0xffffffffu, lim = bc4_setup(x, X, Z);
+    if (wave < 4) bc4_bound<false>(X, Z, tid, bounds[0]);
+    else if (wave < 8) bc4_bound<true>(X, Z, tid - 256, bounds[1]);
+    __syncthreads();
+    bc4_mode<false, true>(X, Z, bounds[0], f, tid, true, kBc4OneWaves, best, pair, lim);
+    bc4_mode<true, true>(X, Z, bounds[1], f, tid, true, kBc4OneWaves, best, pair, lim);
+    const uint64_t key = bc4_key(best, pair);
+    if (lane == 0) keys[wave] = key;
+    __syncthreads();   // and the readers of the bounds are done
+    if (wave == 0) {
+      uint64_t k = keys[0];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const uint64_t o = __shfl_xor(key, off, 64);
-      key = o < key ? o : key;
+      for (int w = 1; w < kBc4OneWaves; ++w) k = keys[w] < k ? keys[w] : k;
+      bc4_write(k, x, lane, job.out + b * 8);
     }
-    if (live && lane < 16) {
-      const int E0 = (int)((key >> 8) & 255u), E1 = (int)(key & 255u);
-      int p[8];
-      bc4_palette8(E0, E1, p);
-      int code = 0, m = INT_MAX;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const int d = p[c] - (int)x;
-        if (d * d < m) {
-          m = d * d;
-          code = c;
-        }
-      }
-      // gather the 16 selectors and pack
-      uint64_t field = (uint64_t)code << (3 * lane);
-      field = (uint64_t)row_or((uint32_t)field) | ((uint64_t)row_or((uint32_t)(field >> 32)) << 32);
-      if (lane == 0) {
-        const uint32_t lo = (uint32_t)E0 | ((uint32_t)E1 << 8) | ((uint32_t)(field & 0xffffu) << 16);
-        *(uint2*)(job.out + b * 8) = make_uint2(lo, (uint32_t)(field >> 16));
-      }
-    }
+    __syncthreads();   // the keys may be written again
   }
 }
 
@@ -920,6 +984,8 @@ int launch_encode(const EncodeJob& ja, const EncodeJob& jb, int codec, int n_cu,
   if (codec == NDGI_CODEC_BC7) {
     const int64_t cap = (int64_t)n_cu * 64;
     hipLaunchKernelGGL(k_encode_bc7, dim3((unsigned)(n < cap ? n : cap)), dim3(kBc7Threads), 0, s, ja, jb);
+  } else if (n <= (int64_t)n_cu * kBc4OnePerCu) {
+    hipLaunchKernelGGL(k_encode_bc4_one, dim3((unsigned)n), dim3(64 * kBc4OneWaves), 0, s, ja, jb);
   } else {
     const int64_t wgs = (n + 3) / 4, cap = (int64_t)n_cu * 64;
     hipLaunchKernelGGL(k_encode_bc4, dim3((unsigned)(wgs < cap ? wgs : cap)), dim3(256), 0, s, ja, jb);
