@@ -1082,8 +1082,15 @@ int ndgi_hybrid_train_step(ndgi_ctx* c, ndgi_hybrid_train_state* st, const ndgi_
     int accum = mode != NDGI_TRAIN_FORWARD && (nthr > 64 || dl.M > 1) && (int64_t)acc_bytes <= kAccMaxBytes &&
                 sw_bytes + slab_bytes + acc_bytes <= (size_t)lds_max;
     // F_uvt's weights as well where they fit (BC7, one word a texel): eight adds a sample that each
-    // would touch a segment of their own
-    if (accum && nthr > 64 && sw_bytes + slab_bytes + acc_bytes + accw_bytes <= (size_t)lds_max) accum = 2;
+    // would touch a segment of their own.  Their words are cleared and written out once a chunk and
+    // leave a CU one workgroup, so a chunk must add a third as often as there are words, or half as
+    // often where there are more workgroups than CUs.  Without and with them, us: 64 M-profile models x
+    // 4096 samples (two thirds) 158 and 154, one model x 131072 (a third) 136 and 133, 8 x 4096 (a sixth)
+    // 47 and 54; beyond a workgroup a CU, L x 100 x 1920 (1.7) 162 and 159, M x 40 x 4096 (a third) 153
+    // and 163, M x 100 x 1920 (0.4) 183 and 264.
+    if (accum && nthr > 64 && sw_bytes + slab_bytes + acc_bytes + accw_bytes <= (size_t)lds_max &&
+        8 * chunk * (wgs <= c->n_cu ? 3 : 2) >= d.o_ut - d.o_tw)
+      accum = 2;
     const size_t dyn_bytes = slab_bytes + (accum ? acc_bytes : 0) + (accum > 1 ? accw_bytes : 0);
     if (mode != NDGI_TRAIN_FORWARD) hipLaunchKernelGGL(k_zero_d, dim3(1), dim3(64), 0, s, loss_dev, 1);
 #define NDGI_HT(HD, M, SIM)                                                                                     \

@@ -374,6 +374,29 @@ def test_every_gradient_sum_at_ragged_sizes_matches_oracle(N, ctx, codec, sizes)
         _close(got[k].cpu().numpy(), ref_g[k], 1e-4, k)
 
 
+def test_short_chunks_keep_their_speed(N, ctx):
+    """100 BC7 M-profile models x 1920 samples (chunks of 640) take little longer than 64 x 4096 (chunks of
+    1024): 1.2 times, and 1.7 where the short chunks also summed F_uvt's weights in LDS."""
+    import torch
+    from paper_2604_12625_amd.train import HybridTrainer
+    keys = I.lightmap_key_times(I.rng(6, I.P_MODEL, 1))
+    st = I.hybrid_train_init(128, 128, "M", len(keys), keys, I.rng(7, I.P_INIT, 1), codec=1)
+    best = {}
+    for models, per in ((100, 1920), (64, 4096)):
+        tr = HybridTrainer(ctx, [st] * models, seed=1, per_model=per)
+        smp = I.train_samples_torch(models * per, 128, 128, len(keys), seed=2, device="cuda")
+        tgt = torch.ones((models, len(keys), 128, 128, 3), device="cuda")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                tr.step(smp, tgt, N.HTRAIN_NOISE)
+            b.record()
+            b.synchronize()
+            best[per] = min(best.get(per, 1e9), a.elapsed_time(b))
+    assert best[1920] <= 1.4 * best[4096], best
+
+
 @pytest.mark.parametrize("hidden", [16, 64])
 def test_rounds_of_a_chunk_equal_separate_calls(N, ctx, hidden):
     """Eight models x 32768 samples run several 256-sample rounds per chunk (four on a
