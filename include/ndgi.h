@@ -126,11 +126,11 @@ int ndgi_get_error_flags(ndgi_ctx* ctx, hipStream_t stream, uint32_t* flags_out)
 int ndgi_bc4_decode_blocks(const uint8_t* blocks, int64_t n, uint8_t* out16, hipStream_t stream);
 
 /* The same decode through one of the texel decoders inside the decode kernels, for checking
- * them exhaustively: impl 0 = the integer decoder above, 1 = the float decoder of the query,
- * page and hybrid kernels (floor(e0 + 0.5 + j (e1 - e0) / D) as one FMA), 2 = the row decoder
- * of the frame and binned kernels (palette built once per block in FP16 packs, four texels
- * per byte permute).  Same layouts and errors as ndgi_bc4_decode_blocks (also impl out of
- * 0..2). */
+ * them exhaustively: impl 0 = the integer decoder above, 1 = the float decoder of the query
+ * kernels of both layouts (floor(e0 + 0.5 + j (e1 - e0) / D) as one FMA), 2 = the row decoder
+ * of the binned and hybrid page kernels (palette built once per block in FP16 packs, four texels
+ * per byte permute; the page kernel takes all four rows of a block from the same palette).  Same
+ * layouts and errors as ndgi_bc4_decode_blocks (also impl out of 0..2). */
 int ndgi_bc4_decode_blocks_impl(const uint8_t* blocks, int64_t n, uint8_t* out16, int32_t impl,
                                 hipStream_t stream);
 

@@ -7,8 +7,9 @@
 namespace ndgi {
 
 // ------------------------------------------------------------------------ BC4 blocks
-// IMPL selects the texel decoder: 0 the integer bc4_texel, 1 the float bc4_texel_f of the
-// query, page and hybrid kernels, 2 the row decode bc4_rows of the frame and binned kernels.
+// IMPL selects the texel decoder: 0 the integer bc4_texel, 1 the float bc4_texel_f of the query
+// kernels (both layouts), 2 the row decode bc4_rows of the binned and hybrid page kernels (the page
+// kernel's bc4_rows4 shares its palette and its pick and takes all four rows).
 template <int IMPL>
 __global__ __launch_bounds__(256) void k_bc4_blocks(const uint8_t* __restrict__ blocks, int64_t n,
                                                      uint8_t* __restrict__ out) {

@@ -73,6 +73,41 @@ def test_kernel_bc4_decoders_exhaustive(N, impl):
     np.testing.assert_array_equal(out, O.bc4_decode_blocks(blocks))
 
 
+@pytest.mark.parametrize("prec,grid", [(1, 256), (0, 10)])
+def test_page_bc4_decoder_exhaustive(N, ctx, prec, grid):
+    """The page kernel's block decoder: the same pairs, selectors and positions as footprint
+    (e0, e1) of a 1024 x 1024 map, channel k with selector (s + k) mod 8 at texel s.  Decoders that
+    output exp(texel / 255) of three channels give the bytes back: a step of one byte is 3.9e-3, the
+    FP16 rounding of the output at most 4.9e-4."""
+    import torch
+    e = np.arange(65536)
+    blocks = np.zeros((65536, 8, 8), dtype=np.uint8)
+    for k in range(8):
+        field = 0
+        for s_ in range(16):
+            field |= ((s_ + k) % 8) << (3 * s_)
+        blocks[:, k, 0] = e >> 8
+        blocks[:, k, 1] = e & 255
+        blocks[:, k, 2:] = np.frombuffer(field.to_bytes(6, "little"), np.uint8)
+    want = O.bc4_decode_blocks(blocks.reshape(-1, 8)).reshape(256, 256, 8, 4, 4).transpose(0, 3, 1, 4, 2)
+    want = want.reshape(1024, 1024, 8)
+    bc4 = torch.from_numpy(blocks.reshape(256, 256, 8, 8)).cuda()
+    nodes = torch.zeros((2, grid, grid, 8), dtype=torch.float16, device="cuda")
+    rq = N.page_requests(*(np.zeros(1, t) for t in (np.int32, np.int32, np.int32, np.float32, np.int64)))
+    one = torch.ones(1, dtype=torch.int32, device="cuda")
+    for ch in ((0, 1, 2), (3, 4, 5), (5, 6, 7)):
+        w1, w2, w3 = np.zeros((32, 16)), np.eye(32), np.zeros((3, 32))
+        for i, c in enumerate(ch):
+            w1[7 * i + c, c] = 1.0
+            w3[i, 7 * i + c] = 1.0
+        mlp = np.concatenate([w1.ravel(), np.zeros(32), w2.ravel(), np.zeros(32), w3.ravel(), np.zeros(3)])
+        dm = N.DeviceModel(1024, 1024, grid, grid, 2, bc4, nodes, torch.from_numpy(mlp.astype(np.float16)).cuda())
+        dst = torch.zeros((1024 * 1024, 3), dtype=torch.float16 if prec else torch.float32, device="cuda")
+        ctx.decode_pages(N.models_array([dm]), 1, rq, one, 1, 1024, dst, 1024, prec)
+        got = torch.round(255 * torch.log(dst.double())).to(torch.int32).cpu().numpy().reshape(1024, 1024, 3)
+        np.testing.assert_array_equal(got, want[..., list(ch)])
+
+
 # --------------------------------------------------------------------------- decode
 def c1_model():
     """64x64 map, grid 16x16x8(t)x8 FP32 U[-1,1], He-normal FP32 decoder (seed 0)."""
