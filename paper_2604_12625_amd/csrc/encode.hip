@@ -521,15 +521,13 @@ __device__ __forceinline__ void m6_search(uint32_t x, const uint32_t X[16], int 
       D[c] = 16 * v - row_sum(v);
       var[c] = lane_of(row_sum(D[c] * D[c]), 0);
     }
-    int ref = 0, vr = var[0], Dr = D[0];
+    int vr = var[0], Dr = D[0];
 #pragma unroll
     for (int c = 1; c < 4; ++c)
       if (var[c] > vr) {
-        ref = c;
         vr = var[c];
         Dr = D[c];
       }
-    (void)ref;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int cov = lane_of(row_sum(D[c] * Dr), 0);

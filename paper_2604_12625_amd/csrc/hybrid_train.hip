@@ -73,11 +73,6 @@ __device__ __forceinline__ float hyb_noise(uint64_t base, uint64_t ctr) {
   return (float)(uint32_t)(x >> 40) * (1.0f / 16777216.0f) - 0.5f;
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 __device__ __forceinline__ double wave_sum_d(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
