@@ -454,40 +454,23 @@ __device__ __forceinline__ h8v texel_x(uint32_t sp, float ga, float gb) {
   return __builtin_bit_cast(h8v, x);
 }
 
-// N (2 or 4) consecutive decoder weights from element i, a multiple of N: at once when the vector
-// is aligned to a quad (VEC), else one by one.  FP16 weights are what gains: a lane's operands
-// are 67 two-byte loads one by one, 19 otherwise, and every wave starts with them.
-template <int MDT, bool VEC, int N>
+// A lane's K shares: inputs input_of(g, 0..3) and units unit_of(g, 0..7) of a weight row at i.  The
+// compiler takes consecutive elements with one load of the vector's own alignment (an FP16 lane has
+// 16 loads for its 67 weights).
+template <int MDT, int N>
 __device__ __forceinline__ void ldn(const void* mlp, int i, float v[N]) {
-  if constexpr (VEC && MDT == NDGI_DTYPE_F16) {
-    typedef _Float16 hnv __attribute__((ext_vector_type(N)));
-    const hnv x = *(const hnv*)((const _Float16*)mlp + i);
 #pragma unroll
-    for (int k = 0; k < N; ++k) v[k] = (float)x[k];
-  } else if constexpr (VEC) {
-    typedef float fnv __attribute__((ext_vector_type(N)));
-    const fnv x = *(const fnv*)((const float*)mlp + i);
-#pragma unroll
-    for (int k = 0; k < N; ++k) v[k] = x[k];
-  } else {
-#pragma unroll
-    for (int k = 0; k < N; ++k) v[k] = ld<MDT>(mlp, i + k);
-  }
+  for (int k = 0; k < N; ++k) v[k] = ld<MDT>(mlp, i + k);
 }
-// Whether a decoder vector is aligned to a quad of its type.
-__device__ __forceinline__ bool mlp_quads(const void* mlp, int dt) {
-  return ((uintptr_t)mlp & (dt == NDGI_DTYPE_F16 ? 7u : 15u)) == 0;
-}
-// A lane's K shares: inputs input_of(g, 0..3) and units unit_of(g, 0..7) of a weight row at i.
-template <int MDT, bool VEC>
+template <int MDT>
 __device__ __forceinline__ void ld_inputs(const void* mlp, int i, int g, float v[4]) {
-  ldn<MDT, VEC, 2>(mlp, i + input_of(g, 0), v);
-  ldn<MDT, VEC, 2>(mlp, i + input_of(g, 2), v + 2);
+  ldn<MDT, 2>(mlp, i + input_of(g, 0), v);
+  ldn<MDT, 2>(mlp, i + input_of(g, 2), v + 2);
 }
-template <int MDT, bool VEC>
+template <int MDT>
 __device__ __forceinline__ void ld_units(const void* mlp, int i, int g, float v[8]) {
-  ldn<MDT, VEC, 4>(mlp, i + unit_of(g, 0), v);
-  ldn<MDT, VEC, 4>(mlp, i + unit_of(g, 4), v + 4);
+  ldn<MDT, 4>(mlp, i + unit_of(g, 0), v);
+  ldn<MDT, 4>(mlp, i + unit_of(g, 4), v + 4);
 }
 
 struct Dec16 {
@@ -501,7 +484,7 @@ struct Dec16 {
 // weights (they multiply the lo halves).  TEXEL = true: slots 0, 1 take hi(W1 * 256/255) of
 // spatial 2g, 2g+1, slots 4, 5 the lo part, slots 2, 3 and 6, 7 the grid weights; c1 has
 // sum_s (hi + lo) removed.  hi stops at the largest FP16 value, which the factor could exceed.
-template <int MDT, bool TEXEL, bool VEC>
+template <int MDT, bool TEXEL>
 __device__ __forceinline__ void load_dec16(Dec16& d, const void* mlp, int lane) {
   const int g = lane >> 4, i = lane & 15;
   float off[2] = {0.0f, 0.0f};   // TEXEL: sum over the spatial inputs of unit 16mc + i, in every group
@@ -509,10 +492,10 @@ __device__ __forceinline__ void load_dec16(Dec16& d, const void* mlp, int lane) 
   for (int mc = 0; mc < 2; ++mc) {
     const int u = 16 * mc + i;
     float w1[4], w2[8], b1[4], b2[4];
-    ld_inputs<MDT, VEC>(mlp, kOffW1 + u * 16, g, w1);
-    ld_units<MDT, VEC>(mlp, kOffW2 + u * 32, g, w2);
-    ldn<MDT, VEC, 4>(mlp, kOffB1 + 16 * mc + 4 * g, b1);
-    ldn<MDT, VEC, 4>(mlp, kOffB2 + 16 * mc + 4 * g, b2);
+    ld_inputs<MDT>(mlp, kOffW1 + u * 16, g, w1);
+    ld_units<MDT>(mlp, kOffW2 + u * 32, g, w2);
+    ldn<MDT, 4>(mlp, kOffB1 + 16 * mc + 4 * g, b1);
+    ldn<MDT, 4>(mlp, kOffB2 + 16 * mc + 4 * g, b2);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float w = w1[e & 3];
@@ -542,7 +525,7 @@ __device__ __forceinline__ void load_dec16(Dec16& d, const void* mlp, int lane) 
   // every load is unconditional (clamped index, then a select): a conditional load would
   // be branched around and serialise the whole set
   float w3[8];
-  ld_units<MDT, VEC>(mlp, kOffW3 + min(i & 3, 2) * 32, g, w3);
+  ld_units<MDT>(mlp, kOffW3 + min(i & 3, 2) * 32, g, w3);
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -583,16 +566,16 @@ struct Dec32 {
   f4v c1[2], c2[2], c3;   // c3: the output bias (the same in every lane)
 };
 
-template <int MDT, bool VEC>
+template <int MDT>
 __device__ __forceinline__ void load_dec32(Dec32& d, const void* mlp, int lane) {
   const int g = lane >> 4, i = lane & 15;
 #pragma unroll
   for (int mc = 0; mc < 2; ++mc) {
     float b1[4], b2[4];
-    ld_inputs<MDT, VEC>(mlp, kOffW1 + (16 * mc + i) * 16, g, d.a1[mc]);
-    ld_units<MDT, VEC>(mlp, kOffW2 + (16 * mc + i) * 32, g, d.a2[mc]);
-    ldn<MDT, VEC, 4>(mlp, kOffB1 + 16 * mc + 4 * g, b1);
-    ldn<MDT, VEC, 4>(mlp, kOffB2 + 16 * mc + 4 * g, b2);
+    ld_inputs<MDT>(mlp, kOffW1 + (16 * mc + i) * 16, g, d.a1[mc]);
+    ld_units<MDT>(mlp, kOffW2 + (16 * mc + i) * 32, g, d.a2[mc]);
+    ldn<MDT, 4>(mlp, kOffB1 + 16 * mc + 4 * g, b1);
+    ldn<MDT, 4>(mlp, kOffB2 + 16 * mc + 4 * g, b2);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       d.c1[mc][r] = b1[r];
@@ -600,7 +583,7 @@ __device__ __forceinline__ void load_dec32(Dec32& d, const void* mlp, int lane) 
     }
   }
 #pragma unroll
-  for (int c = 0; c < 3; ++c) ld_units<MDT, VEC>(mlp, kOffW3 + c * 32, g, d.w3[c]);
+  for (int c = 0; c < 3; ++c) ld_units<MDT>(mlp, kOffW3 + c * 32, g, d.w3[c]);
 #pragma unroll
   for (int r = 0; r < 4; ++r) d.c3[r] = r < 3 ? ld<MDT>(mlp, kOffB3 + r) : 0.0f;
 }
@@ -648,11 +631,8 @@ template <> struct Dec<NDGI_PREC_F16> {
   typedef f4v Acc;
   template <bool TEXEL>
   __device__ __forceinline__ void load_as(const void* mlp, int dt, int lane) {
-    const bool f16 = dt == NDGI_DTYPE_F16, vec = mlp_quads(mlp, dt);
-    if (f16 && vec) load_dec16<NDGI_DTYPE_F16, TEXEL, true>(d, mlp, lane);
-    else if (f16) load_dec16<NDGI_DTYPE_F16, TEXEL, false>(d, mlp, lane);
-    else if (vec) load_dec16<NDGI_DTYPE_F32, TEXEL, true>(d, mlp, lane);
-    else load_dec16<NDGI_DTYPE_F32, TEXEL, false>(d, mlp, lane);
+    if (dt == NDGI_DTYPE_F16) load_dec16<NDGI_DTYPE_F16, TEXEL>(d, mlp, lane);
+    else load_dec16<NDGI_DTYPE_F32, TEXEL>(d, mlp, lane);
   }
   __device__ __forceinline__ void load(const void* mlp, int dt, int lane) { load_as<false>(mlp, dt, lane); }
   // weights for texel centres (see load_dec16), used with texel_group
@@ -673,11 +653,8 @@ template <> struct Dec<NDGI_PREC_F32> {
     float z[4][3];
   };
   __device__ __forceinline__ void load(const void* mlp, int dt, int lane) {
-    const bool f16 = dt == NDGI_DTYPE_F16, vec = mlp_quads(mlp, dt);
-    if (f16 && vec) load_dec32<NDGI_DTYPE_F16, true>(d, mlp, lane);
-    else if (f16) load_dec32<NDGI_DTYPE_F16, false>(d, mlp, lane);
-    else if (vec) load_dec32<NDGI_DTYPE_F32, true>(d, mlp, lane);
-    else load_dec32<NDGI_DTYPE_F32, false>(d, mlp, lane);
+    if (dt == NDGI_DTYPE_F16) load_dec32<NDGI_DTYPE_F16>(d, mlp, lane);
+    else load_dec32<NDGI_DTYPE_F32>(d, mlp, lane);
   }
   __device__ __forceinline__ void load_texel(const void* mlp, int dt, int lane) { load(mlp, dt, lane); }
   __device__ __forceinline__ Acc start() const { return Acc(); }
