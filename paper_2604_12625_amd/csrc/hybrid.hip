@@ -33,12 +33,9 @@ struct HybTab {
 
 // Build the decoder table of a model (all threads of the workgroup; the caller
 // synchronises before use).
-// Every quad of weights starts at a multiple of 4 elements: VEC (the vector is aligned to a quad)
-// loads it at once.
-template <int PREC, int HD, int MDT, bool VEC>
+template <int PREC, int HD, int MDT>
 __device__ void hyb_build_dt(HybTab<HD>& T, const void* mlp) {
   using S = HybShape<HD>;
-  static_assert(S::oW2 % 4 == 0 && S::oW3 % 4 == 0, "quads of weights stay aligned");
   for (int idx = threadIdx.x; idx < S::kChunks * 64; idx += blockDim.x) {
     const int c = idx >> 6, lane = idx & 63, g = lane >> 4, i = lane & 15;
     int base, kbase;   // offset of the row in the packed vector (or -1 for a zero row), first unit
@@ -55,22 +52,11 @@ __device__ void hyb_build_dt(HybTab<HD>& T, const void* mlp) {
       base = (i & 3) < 3 ? S::oW3 + (i & 3) * HD : -1;
       kbase = 16 * kb + 4 * g;
     }
-    // loads are unconditional (clamped row), the zero rows select afterwards
+    // loads are unconditional (clamped row) and so one load a quad; the zero rows select afterwards
     const int row = base < 0 ? S::oW3 : base;
     float w[4];
-    if constexpr (VEC && MDT == NDGI_DTYPE_F16) {
-      typedef _Float16 h4v __attribute__((ext_vector_type(4)));
-      const h4v x = *(const h4v*)((const _Float16*)mlp + row + kbase);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) w[r] = (float)x[r];
-    } else if constexpr (VEC) {
-      const f4v x = *(const f4v*)((const float*)mlp + row + kbase);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) w[r] = x[r];
-    } else {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) w[r] = ld<MDT>(mlp, row + kbase + r);
-    }
+    for (int r = 0; r < 4; ++r) w[r] = ld<MDT>(mlp, row + kbase + r);
 #pragma unroll
     for (int r = 0; r < 4; ++r) w[r] = base < 0 ? 0.0f : w[r];
     if constexpr (PREC == NDGI_PREC_F16) {
@@ -91,11 +77,8 @@ __device__ void hyb_build_dt(HybTab<HD>& T, const void* mlp) {
 
 template <int PREC, int HD>
 __device__ void hyb_build(HybTab<HD>& T, const void* mlp, int mlp_dtype) {
-  const bool f16 = mlp_dtype == NDGI_DTYPE_F16, vec = ((uintptr_t)mlp & (f16 ? 7u : 15u)) == 0;
-  if (f16 && vec) hyb_build_dt<PREC, HD, NDGI_DTYPE_F16, true>(T, mlp);
-  else if (f16) hyb_build_dt<PREC, HD, NDGI_DTYPE_F16, false>(T, mlp);
-  else if (vec) hyb_build_dt<PREC, HD, NDGI_DTYPE_F32, true>(T, mlp);
-  else hyb_build_dt<PREC, HD, NDGI_DTYPE_F32, false>(T, mlp);
+  if (mlp_dtype == NDGI_DTYPE_F16) hyb_build_dt<PREC, HD, NDGI_DTYPE_F16>(T, mlp);
+  else hyb_build_dt<PREC, HD, NDGI_DTYPE_F32>(T, mlp);
 }
 
 // A lane's operands of the decoder: read from the table where they are used, or (h = 16: three
@@ -476,8 +459,8 @@ __host__ __device__ inline bool hybrid_ok(const ndgi_hybrid_model& m) {
 // phase, the decoder after the handoff); the decoder table and the key table are built
 // once per workgroup in LDS.  Bound by vector instructions (about 10 an activation, 18 a
 // BC4 tap and channel) and, for small n, by the table's build.  300007 queries, h = 64, FP16, BC4
-// layout: 43.2 us with the weights loaded one by one and four output accumulators' rows masked
-// in, 35.8 with quads loaded at once and the outputs selected; h = 16, BC7: 18.1 and 17.2.  At
+// layout: 43.2 us with the weights loaded one by one (conditionally) and four output accumulators'
+// rows masked in, 35.8 with one load a quad and the outputs selected; h = 16, BC7: 18.1 and 17.2.  At
 // most 128 registers (4 waves a SIMD): 154 without the bound, for 12 blocks in flight.
 template <int PREC, int HD, int CD>
 __global__ __launch_bounds__(256, 4) void k_hybrid_query(ndgi_hybrid_model m, const float* __restrict__ uvt, int64_t n,
@@ -529,7 +512,8 @@ __global__ __launch_bounds__(256, 4) void k_hybrid_query(ndgi_hybrid_model m, co
 // activations (784 with the F_uv block decoded by every texel of it).  64 M-profile BC7 tiles of
 // 136 x 136 texels, FP16: 35.1 us before, 31.5 with the blocks decoded once, the operands of an
 // h = 16 decoder in registers and the table's quads loaded at once; about 8 of them are the launch
-// and the chain request -> model -> table.  5 workgroups a CU spill (34.0).  Texel-centre axes use exact integer arithmetic (texel_axis).
+// and the chain request -> model -> table.  5 workgroups a CU spill (34.0).  Texel-centre axes use
+// exact integer arithmetic (texel_axis).
 constexpr int kHybSub = 34;
 constexpr int kHybWin = kHybSub + 1;
 constexpr int kHybBlocks = (kHybSub + 3 + 3) / 4;   // footprints that kHybSub texels can touch along one axis
