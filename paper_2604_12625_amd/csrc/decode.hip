@@ -92,26 +92,40 @@ int launch_decode(ndgi_ctx* ctx, const ndgi_model& m, const float* uvt, int64_t 
   // each other's lines: workgroups a CU where all that is resident would be slower (us, all resident
   // and this):
   //  * FP16, FP16 grid: 2 (1M queries of 256^2 x 24 60.7 and 54.2, of 1024^2 115 and 103, 16M of
-  //    4096^2 2250 and 1990); a model that lies in the CUs' own caches takes all (3M of 64^2 x 8: 108,
-  //    with two 119).
+  //    4096^2 2250 and 1990); of a model that lies in the CUs' own caches, on either grid and after some
+  //    rounds, all (3M of 64^2 x 8: 108, with two 119).
   //  * FP16, FP32 grid: 3 (1M of 512^2 98.5 and 92.5), or 2 where the model exceeds the chip's 32 MB
-  //    of L2 and there are rounds to spread over (1M of 1024^2 128 and 114).
+  //    of L2 and there are rounds to spread over (1M of 1024^2 128 and 111).
   //  * FP32, FP16 grid: 2 (1M of 4096^2 145 and 133), or 3 for a model within an XCD's L2 and many
   //    rounds, which is bound by the decoder (3M of 256^2: 176, with two 182).
-  //  * FP32, FP32 grid: 3 (1M of 512^2 102 and 98).
-  // In FP16 up to a quarter of a workgroup a CU beyond that goes with the round: as a round of its own it
-  // would leave the chip idle (131073 queries on an FP32 grid of 512^2: 16.9, cut into two rounds 20.4).
+  //  * FP32, FP32 grid: 3 (1M of 512^2 102 and 98), or all for such models and counts (3M of 256^2: 193,
+  //    with three 200).
+  // Three a CU that take as many rounds as two are two (200003 queries of 1024^2, FP32 grid, FP16: 33.6
+  // and 29.3).  In FP16 up to a quarter of a workgroup a CU beyond a round goes with it: as a round of its
+  // own it would leave the chip idle (131073 queries on an FP32 grid of 512^2: 16.9, cut into two 20.4).
+  // Where the last round would put as many workgroups on some CUs as a full one, the rounds are made
+  // equal: no CU takes more for it, and fewer waves are in flight (200003 queries of 2048^2 x 24, FP16,
+  // 32.1 and 29.5; 1M 117 and 114).  Where it would put fewer, equal rounds cost a pass on every CU
+  // (262145 of 512^2 26.0 and 32.6).
   const int64_t cu = ctx->n_cu, bytes = (int64_t)m.W * m.H * 4 + (int64_t)m.T * m.Gh * m.Gw * (g16 ? 16 : 32);
-  int64_t per_cu = 3, slack = 0;
+  const auto rounds_of = [&](int64_t c) { return (wgs + c * cu - 1) / (c * cu); };
+  int64_t per_cu, slack = 0;
   if (prec == NDGI_PREC_F16) {
-    per_cu = g16 ? (bytes > (128 << 10) ? 2 : 4) : (bytes > (32 << 20) && wgs > 5 * cu ? 2 : 3);
+    per_cu = g16 || (bytes > (32 << 20) && wgs > 5 * cu) ? 2 : 3;
+    if (bytes <= (128 << 10) && wgs > 9 * cu) per_cu = 4;
     slack = cu / 4;
   } else if (g16) {
     per_cu = bytes <= (2 << 20) && wgs > 12 * cu ? 3 : 2;
+  } else {
+    per_cu = bytes <= (4 << 20) && wgs > 12 * cu ? 4 : 3;
   }
+  if (per_cu == 3 && wgs > 3 * cu + cu / 64 && rounds_of(2) == rounds_of(3)) per_cu = 2;
   const int64_t resident = resident_wgs(ctx, kern);
   const int64_t cap = wgs > per_cu * cu + slack ? std::min(resident, per_cu * cu) : resident;
-  if (wgs > cap) wgs = cap;
+  if (wgs > cap) {
+    const int64_t rounds = (wgs + cap - 1) / cap, last = wgs - (rounds - 1) * cap;
+    wgs = last > cap - cu + cu / 64 ? (wgs + rounds - 1) / rounds : cap;
+  }
   if (prec == NDGI_PREC_F16 && g16)
     hipLaunchKernelGGL((k_decode_query<NDGI_PREC_F16, NDGI_DTYPE_F16>), dim3((unsigned)wgs), dim3(256), 0, s, m, uvt, n, out);
   else if (prec == NDGI_PREC_F16)
