@@ -65,7 +65,9 @@ __device__ __forceinline__ float gelu(float x) {
 
 // GELU and its derivative Phi(x) + x phi(x) for training, in FP32: Phi from the same
 // erfc (Phi(x) = erfc(-x / sqrt 2) / 2), phi = exp(-x^2 / 2) / sqrt(2 pi).  What is fused is
-// written out, so that the value does not change with the code around a call.
+// written out, so that the value does not change with the code around a call: for x >= 0 Phi is
+// 1 - t exp(..) with the product rounded first, or (FUSED) not.
+template <bool FUSED>
 __device__ __forceinline__ float gelu_grad(float x) {
 #pragma clang fp contract(off)
   using namespace gelu_k;
@@ -76,7 +78,8 @@ __device__ __forceinline__ float gelu_grad(float x) {
   for (int i = 2; i < 10; ++i) p = fmaf(t, p, kNRf[i]);
   const float e2 = __builtin_amdgcn_exp2f(x * x * (float)(-0.5 * kLog2e));   // exp(-x^2 / 2)
   const float q = __builtin_amdgcn_exp2f(fmaf(x * x, (float)(-0.5 * kLog2e), p)), half_erfc = t * q;
-  const float phi_cdf = x >= 0.0f ? fmaf(-t, q, 1.0f) : half_erfc;
+  const float upper = FUSED ? fmaf(-t, q, 1.0f) : 1.0f - half_erfc;
+  const float phi_cdf = x >= 0.0f ? upper : half_erfc;
   return fmaf(x, e2 * (float)(0.39894228040143268), phi_cdf);   // 1 / sqrt(2 pi)
 }
 

@@ -537,7 +537,7 @@ __global__ __launch_bounds__(kHtMaxThreads) void k_hybrid_train(HybTrainDims d, 
         for (int q = 0; q < 4; ++q) {
           const f4v dh = __builtin_amdgcn_mfma_f32_16x16x4f32(wt, dq[q], f4v{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) a2[k][q][r] = dh[r] * gelu_grad(a2[k][q][r]);
+          for (int r = 0; r < 4; ++r) a2[k][q][r] = dh[r] * gelu_grad<false>(a2[k][q][r]);
         }
       }
       // Layers 2 and 1, one 16-unit block k of layer 1 at a time: dW2[j][k] = sum g2[j] h1[k]
@@ -584,7 +584,8 @@ __global__ __launch_bounds__(kHtMaxThreads) void k_hybrid_train(HybTrainDims d, 
         for (int q = 0; q < 4; ++q)
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            t[q][r] *= gelu_grad(a1[k][q][r]);   // now g1
+            // (h = 16 has always had the fused form, h = 64 the other)
+            t[q][r] *= gelu_grad<HD == 16>(a1[k][q][r]);   // now g1
         slab_store(slA, lane, t);
         slab_store(slB, lane, xq);
         wave_sync();
