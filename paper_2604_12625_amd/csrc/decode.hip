@@ -152,12 +152,13 @@ int launch_decode(ndgi_ctx* ctx, const ndgi_model& m, const float* uvt, int64_t 
 //    into a row sample, one row ahead of use; a texel row is then one lerp between the two
 //    row samples around it.  No grid value goes through LDS, and a row sample serves every
 //    texel row that it bounds.
-// The precision's decoder takes it from there.  Bound by VALU and matrix issue: about 224 VALU
-// and 32 MFMA a pass in FP16 (a kernel that staged each pass's time-blended grid window in LDS
-// took 250, and the maps off its quarter-resolution FP16 grid went to a second kernel, launched
-// after it in any case).  4096^2 FP16 frame 207 -> 191 us, 2000 pages of 32 maps 440 -> 397 us;
-// 1600 x 1152 in FP32 with a grid at an eighth of the texels 125 -> 73 us (there each texel
-// took its two texel_axis divisions, two integer block decodes and eight node loads alone).
+// The precision's decoder takes it from there.  FP16: 271 vector instructions a pass, 32 of them
+// MFMA (294 by a kernel that staged each pass's time-blended grid window in LDS, beside a second
+// kernel, launched after it in any case, for maps off its quarter-resolution FP16 grid).  The VALU is
+// busy 73% of the time and the matrix cores 27%; a wave waits 42% of its time to issue and 19% for
+// memory.  4096^2 FP16 frame 207 -> 190 us, 2000 pages of 32 maps 437 -> 390 us.  FP32 is bound by
+// matrix time (busy 62%): 1600 x 1152 with a grid at an eighth of the texels 125 -> 73 us (there each
+// texel took its two texel_axis divisions, two integer block decodes and eight node loads alone).
 // Measured and not kept: the passes dealt out in equal contiguous runs, or in rounds of equal
 // parts of a run, instead of sub-tiles round-robin (197-209 us for the frame: more slab starts,
 // and neighbouring columns' lines written by different waves).
