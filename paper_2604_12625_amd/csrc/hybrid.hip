@@ -508,12 +508,12 @@ __global__ __launch_bounds__(256, 4) void k_hybrid_query(ndgi_hybrid_model m, co
 //  * per sub-tile column: its F_uvt taps and weight and its V_ut (F_ut blended in time,
 //    then along u); per row: its F_uvt taps and weight and its V_vt;
 // then each pass of a wave decodes 64 consecutive texels of the sub-tile (row-major) from
-// LDS alone.  Bound by vector instructions: 449 a pass and lane, 340 of them the 32
-// activations (784 with the F_uv block decoded by every texel of it).  64 M-profile BC7 tiles of
-// 136 x 136 texels, FP16: 35.1 us before, 31.5 with the blocks decoded once, the operands of an
-// h = 16 decoder in registers and the table's quads loaded at once; about 8 of them are the launch
-// and the chain request -> model -> table.  5 workgroups a CU spill (34.0).  Texel-centre axes use
-// exact integer arithmetic (texel_axis).
+// LDS alone.  Bound by vector instructions: 449 in the loop over passes, 340 of them the 32
+// activations, 634 a pass over all (708 with the F_uv block decoded by every texel of it).  64
+// M-profile BC7 tiles of 136 x 136 texels, FP16: 35.1 us before, 31.5 with the blocks decoded once,
+// the operands of an h = 16 decoder in registers and the table's quads loaded at once; about 8 of them
+// are the launch and the chain request -> model -> table.  5 workgroups a CU spill (34.0).
+// Texel-centre axes use exact integer arithmetic (texel_axis).
 constexpr int kHybSub = 34;
 constexpr int kHybWin = kHybSub + 1;
 constexpr int kHybBlocks = (kHybSub + 3 + 3) / 4;   // footprints that kHybSub texels can touch along one axis
